@@ -1052,32 +1052,26 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     }
 
     // ---- descriptor ----
-    KDesc d;
-    memset(&d, 0, sizeof(d));
+    KDesc d = {};
+    auto dim = [](int64_t e, int64_t s0, int64_t s1) {
+        return KDim{(int32_t)e, recip(e), 0, s0, s1};
+    };
     d.sizeX = sizeX;
     d.sizeY = sizeY;
     d.nx = (int)Ix.size();
     d.ny = (int)Iy.size();
-    for (int i = 0; i < d.nx; ++i) {
-        d.extX[i] = (int32_t)Ix[i].extent;
-        d.strXop[i] = sX(Ix[i]);
-        d.strCx[i] = Ix[i].strC;
-    }
-    for (int i = 0; i < d.ny; ++i) {
-        d.extY[i] = (int32_t)Iy[i].extent;
-        d.strYop[i] = sY(Iy[i]);
-        d.strCy[i] = Iy[i].strC;
-    }
+    for (int i = 0; i < d.nx; ++i)
+        d.x[i] = dim(Ix[i].extent, sX(Ix[i]), Ix[i].strC);
+    for (int i = 0; i < d.ny; ++i)
+        d.y[i] = dim(Iy[i].extent, sY(Iy[i]), Iy[i].strC);
     d.nk = nk;
-    for (int i = 0; i < nk; ++i) {
-        d.extK[i] = (int32_t)Ik[i].extent;
-        d.strXk[i] = sX(Ik[i]);
-        d.strYk[i] = sY(Ik[i]);
-    }
+    for (int i = 0; i < nk; ++i)
+        d.k[i] = dim(Ik[i].extent, sX(Ik[i]), sY(Ik[i]));
     d.kj = kj;
     d.tj = (int32_t)tj;
     d.kbox = (int32_t)kbox;
     d.nblk = (int32_t)std::max<int64_t>(nblk, 1);
+    d.nblkInv = recip(d.nblk);
     d.nsteps = nsteps;
     const int64_t tilesX = (sizeX + ts.mt - 1) / ts.mt;
     const int64_t tilesY = (sizeY + ts.nt - 1) / ts.nt;
@@ -1087,6 +1081,9 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     d.tilesX = (int32_t)tilesX;
     d.tilesY = (int32_t)tilesY;
     d.group = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, tilesX));
+    d.tilesYInv = recip(tilesY);
+    d.bandInv = recip((int64_t)d.group * tilesY);
+    d.groupInv = recip(d.group);
     d.order = streaming ? 1 : 0;
     d.xcdremap = -1;   // decided per call (see gett_contract)
     if (const char *xr = hk.xcdRemap) d.xcdremap = atoi(xr) != 0;   // tuning hook

@@ -32,30 +32,57 @@ enum GatherMode : int {
     kGatherKVecStrided = 4
 };
 
+// Division of v < 2^31 by a divisor known to the host: q = (v * mag) >> 32 >> sh
+// with sh = ceil(log2 n) - 1 and mag = floor(2^(32 + sh) / n) + 1 (Granlund and
+// Montgomery, "Division by Invariant Integers using Multiplication"; mag * n
+// exceeds 2^(32 + sh) by at most n <= 2^(sh + 1), so the error v * n / 2^(32 +
+// sh) / n stays below 1 / n).  n = 1 has no such multiplier below 2^32; it is
+// left at mag = 0 (q = 0): an index of extent 1 stands for an empty set, whose
+// only position is 0.  On the device it is a multiplication and a shift in
+// place of the twenty-odd instructions of a division.
+struct Recip {
+    uint32_t mag = 0;
+    uint32_t sh = 0;
+};
+inline Recip recip(int64_t n)
+{
+    Recip r;
+    if (n < 2) return r;
+    while (((int64_t)2 << r.sh) < n) ++r.sh;
+    r.mag = (uint32_t)((((uint64_t)1 << (32 + r.sh)) / (uint64_t)n) + 1);
+    return r;
+}
+
+// One index of a set: its extent with the reciprocal, and its strides in the
+// two tensors that hold it -- the operand and C (free sets), X and Y (the
+// contracted set).  Kept together, so that one wide scalar load fetches it.
+struct KDim {
+    int32_t ext;
+    Recip inv;
+    int32_t pad;
+    int64_t s0, s1;
+};
+
 struct KDesc {
     // ---- free sets, linearised ----
     int64_t sizeX;                 // S_{I_x}
     int64_t sizeY;                 // S_{I_y}
     int32_t nx, ny;                // number of (merged) indices in each set
-    int32_t extX[kMaxDims];        // extents, first = fastest in the linear order
-    int32_t extY[kMaxDims];
-    int64_t strXop[kMaxDims];      // stride of each x index in X
-    int64_t strCx[kMaxDims];       // stride of each x index in C
-    int64_t strYop[kMaxDims];      // stride of each y index in Y
-    int64_t strCy[kMaxDims];       // stride of each y index in C
+    KDim x[kMaxDims];              // first = fastest in the linear order; s0: X, s1: C
+    KDim y[kMaxDims];              // s0: Y, s1: C
     // ---- contracted set, walked as K boxes ----
     int32_t nk;                    // number of (merged) contracted indices (>= 1)
-    int32_t extK[kMaxDims];
-    int64_t strXk[kMaxDims];       // stride of each contracted index in X
-    int64_t strYk[kMaxDims];       // stride in Y
+    KDim k[kMaxDims];              // s0: X, s1: Y
     int32_t kj;                    // index that is blocked (earlier ones are whole)
     int32_t tj;                    // block length along index kj
-    int32_t kbox;                  // elements in one box = prod(extK[0..kj-1]) * tj
-    int32_t nblk;                  // blocks along index kj = ceil(extK[kj] / tj)
-    int64_t nsteps;                // boxes = nblk * prod(extK[kj+1..nk-1]); 0 = empty sum
+    int32_t kbox;                  // elements in one box = prod(earlier extents) * tj
+    int32_t nblk;                  // blocks along index kj = ceil(extent of kj / tj)
+    Recip nblkInv;
+    int64_t nsteps;                // boxes = nblk * prod(later extents); 0 = empty sum
     // ---- grid ----
     int32_t tilesX, tilesY;        // tiles along x and y
     int32_t group;                 // tiles along x that share a column band (L2 reuse)
+    Recip tilesYInv, bandInv, groupInv;   // of tilesY, group * tilesY and group
     int32_t order;                 // 0: banded tile walk, 1: y-fastest walk (C stream order)
     int32_t xcdremap;              // 1: consecutive tiles on one XCD, 0: hardware order
                                    // (-1 in a plan: chosen per call)

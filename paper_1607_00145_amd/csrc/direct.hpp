@@ -189,15 +189,16 @@ struct DirectWalk {
 
     __device__ __forceinline__ void init(const KDesc &d)
     {
+        const KDim &kj = d.k[d.kj];
         nblk = d.nblk > 0 ? d.nblk : 1;
-        ek = d.extK[d.kj];
+        ek = kj.ext;
         tj = d.tj;
-        bx = (int64_t)d.tj * d.strXk[d.kj];
-        by = (int64_t)d.tj * d.strYk[d.kj];
+        bx = (int64_t)d.tj * kj.s0;
+        by = (int64_t)d.tj * kj.s1;
         const bool later = d.kj + 1 < d.nk;
-        e1 = later ? d.extK[d.kj + 1] : 0;
-        sx1 = later ? d.strXk[d.kj + 1] : 0;
-        sy1 = later ? d.strYk[d.kj + 1] : 0;
+        e1 = later ? d.k[d.kj + 1].ext : 0;
+        sx1 = later ? d.k[d.kj + 1].s0 : 0;
+        sy1 = later ? d.k[d.kj + 1].s1 : 0;
         next = 0;
         blk = 0;
         c1 = 0;

@@ -73,6 +73,22 @@ constexpr int kInvalidK = 0x7fffffff;
 // (expcnt 7, lgkmcnt 15; gfx9 encoding).
 constexpr int kWaitStores = (7 << 4) | (15 << 8);
 
+// v / n for v < 2^31 with the host's reciprocal of n (n = 1 included).
+__device__ __forceinline__ uint32_t quotient(uint32_t v, int n, Recip r)
+{
+    return n == 1 ? v : __umulhi(v, r.mag) >> r.sh;
+}
+// Position v of a linearised set, its first index split off: returns that
+// index's value and leaves the position over the later ones in v.  (An index
+// of extent 1 stands for an empty set: its value is 0 and v is 0.)
+__device__ __forceinline__ uint32_t digit(uint32_t &v, const KDim &i)
+{
+    const uint32_t q = __umulhi(v, i.inv.mag) >> i.inv.sh;
+    const uint32_t c = v - q * (uint32_t)i.ext;
+    v = q;
+    return c;
+}
+
 // Map the hardware workgroup id to a tile.  Workgroups are dealt round-robin
 // to the 8 XCDs (each with its own L2); renumber so that consecutive logical
 // tiles run on one XCD.  Then either walk tiles in bands of `group` x-tiles,
@@ -86,16 +102,17 @@ __device__ __forceinline__ void tile_of_block(const KDesc &d, int bid, int nwg, 
     int logical = bid;
     if (d.xcdremap && bid < full) logical = (bid & 7) * (full >> 3) + (bid >> 3);
     if (d.order == 1) {
-        tx = logical / d.tilesY;
+        tx = (int)quotient((uint32_t)logical, d.tilesY, d.tilesYInv);
         ty = logical - tx * d.tilesY;
         return;
     }
     const int band = d.group * d.tilesY;
-    const int first = (logical / band) * d.group;
-    const int gsz = min(d.tilesX - first, d.group);
-    const int in = logical - (logical / band) * band;
-    tx = first + in % gsz;
-    ty = in / gsz;
+    const int b = (int)quotient((uint32_t)logical, band, d.bandInv);
+    const int first = b * d.group;
+    const int in = logical - b * band;
+    const int gsz = min(d.tilesX - first, d.group);   // the last band may be narrower
+    ty = gsz == d.group ? (int)quotient((uint32_t)in, d.group, d.groupInv) : in / gsz;
+    tx = first + in - ty * gsz;
 }
 
 // Origin of K box `s`: block `s % nblk` of index kj, then one point of each
@@ -104,21 +121,18 @@ __device__ __forceinline__ void tile_of_block(const KDesc &d, int bid, int nwg, 
 // valid positions left along index kj.
 __device__ __forceinline__ int box_origin(const KDesc &d, uint32_t s, int64_t &ox, int64_t &oy)
 {
-    const uint32_t nb = (uint32_t)d.nblk;
-    const uint32_t rest0 = s / nb;
-    const int blk = (int)(s - rest0 * nb);
-    uint32_t rest = rest0;
-    ox = (int64_t)(blk * d.tj) * d.strXk[d.kj];
-    oy = (int64_t)(blk * d.tj) * d.strYk[d.kj];
+    const KDim &kj = d.k[d.kj];
+    uint32_t rest = quotient(s, d.nblk, d.nblkInv);
+    const int blk = (int)(s - rest * (uint32_t)d.nblk);
+    ox = (int64_t)(blk * d.tj) * kj.s0;
+    oy = (int64_t)(blk * d.tj) * kj.s1;
     for (int i = d.kj + 1; i < d.nk; ++i) {
-        const uint32_t e = (uint32_t)d.extK[i];
-        const uint32_t q = rest / e;
-        const uint32_t c = rest - q * e;
-        rest = q;
-        ox += (int64_t)c * d.strXk[i];
-        oy += (int64_t)c * d.strYk[i];
+        const KDim &k = d.k[i];
+        const uint32_t c = digit(rest, k);
+        ox += (int64_t)c * k.s0;
+        oy += (int64_t)c * k.s1;
     }
-    return d.extK[d.kj] - blk * d.tj;
+    return kj.ext - blk * d.tj;
 }
 
 // Origins of consecutive K boxes without a division per box: the block
@@ -140,20 +154,22 @@ struct BoxWalker {
     {
         cur = s;
         lim = box_origin(d, s, ox, oy);
-        blk = (int)(s % (uint32_t)nblk);
-        c1 = e1 > 0 ? (int)((s / (uint32_t)nblk) % (uint32_t)e1) : 0;
+        uint32_t rest = quotient(s, nblk, d.nblkInv);
+        blk = (int)(s - rest * (uint32_t)nblk);
+        c1 = e1 > 0 ? (int)digit(rest, d.k[d.kj + 1]) : 0;
     }
     __device__ __forceinline__ void init(const KDesc &d, uint32_t s)
     {
+        const KDim &kj = d.k[d.kj];
         nblk = d.nblk > 0 ? d.nblk : 1;
         tj = d.tj;
-        ek = d.extK[d.kj];
-        bx = (int64_t)d.tj * d.strXk[d.kj];
-        by = (int64_t)d.tj * d.strYk[d.kj];
+        ek = kj.ext;
+        bx = (int64_t)d.tj * kj.s0;
+        by = (int64_t)d.tj * kj.s1;
         const bool later = d.kj + 1 < d.nk;
-        e1 = later ? d.extK[d.kj + 1] : 0;
-        sx1 = later ? d.strXk[d.kj + 1] : 0;
-        sy1 = later ? d.strYk[d.kj + 1] : 0;
+        e1 = later ? d.k[d.kj + 1].ext : 0;
+        sx1 = later ? d.k[d.kj + 1].s0 : 0;
+        sy1 = later ? d.k[d.kj + 1].s1 : 0;
         reset(d, s);
     }
     // origin of box s (returns the valid positions along kj)
@@ -399,20 +415,18 @@ template <int R> __device__ __forceinline__ int block_row(int b, int rho)
 // range relative to it are then >= 0, and the analyser bounds them by 2^31 - 1
 // (the tile's own span), so the per-tile tables hold 32-bit offsets while the
 // tensors may be larger.
-__device__ __forceinline__ void range_base(int n, const int32_t *ext, const int64_t *sop,
-                                           const int64_t *sc, uint32_t x0, uint32_t x1,
+__device__ __forceinline__ void range_base(int n, const KDim *set, uint32_t x0, uint32_t x1,
                                            int64_t &bop, int64_t &bc)
 {
     bop = 0;
     bc = 0;
     for (int i = 0; i < n; ++i) {
-        const uint32_t e = (uint32_t)ext[i];
-        const uint32_t q0 = x0 / e, q1 = x1 / e;
-        const int64_t dmin = q0 == q1 ? (int64_t)(x0 - q0 * e) : 0;
-        bop += dmin * sop[i];
-        bc += dmin * sc[i];
-        x0 = q0;
-        x1 = q1;
+        const KDim &k = set[i];
+        const uint32_t c = digit(x0, k);
+        (void)digit(x1, k);
+        const int64_t dmin = x0 == x1 ? (int64_t)c : 0;
+        bop += dmin * k.s0;
+        bc += dmin * k.s1;
     }
 }
 
@@ -440,8 +454,8 @@ __device__ __forceinline__ TileBase tile_base(const KDesc &d, int tx, int ty)
     const uint32_t x0 = (uint32_t)(uniform(tx) * MT), y0 = (uint32_t)(uniform(ty) * NT);
     const uint32_t x1 = (uint32_t)min((int64_t)x0 + MT, d.sizeX) - 1;
     const uint32_t y1 = (uint32_t)min((int64_t)y0 + NT, d.sizeY) - 1;
-    range_base(d.nx, d.extX, d.strXop, d.strCx, x0, x1, b.x, b.cx);
-    range_base(d.ny, d.extY, d.strYop, d.strCy, y0, y1, b.y, b.cy);
+    range_base(d.nx, d.x, x0, x1, b.x, b.cx);
+    range_base(d.ny, d.y, y0, y1, b.y, b.cy);
     b.x = uniform(b.x);
     b.cx = uniform(b.cx);
     b.y = uniform(b.y);
@@ -451,7 +465,8 @@ __device__ __forceinline__ TileBase tile_base(const KDesc &d, int tx, int ty)
 
 // identify_subtensor for one tile: operand and C offsets of every tile row
 // (x side) and column (y side), relative to the tile's base offsets, one
-// mixed-radix decomposition each.
+// mixed-radix decomposition each.  The offsets fit 31 bits (the analyser
+// checks the tile's span), so they are formed modulo 2^32.
 template <int MT, int NT, int NTH>
 __device__ __forceinline__ void tile_tables(const KDesc &d, int tx, int ty, const TileBase &b,
                                             int tid, int *rowX, int *offCx, int *rowY, int *offCy)
@@ -459,42 +474,30 @@ __device__ __forceinline__ void tile_tables(const KDesc &d, int tx, int ty, cons
     // the x and y sides in separate branches: each reads its descriptor
     // arrays at wave-uniform indices (scalar loads, which do not wait behind
     // the wavefront's vector memory instructions in flight)
-    auto decode = [](uint32_t v, int n, const int32_t *ext, const int64_t *so, const int64_t *sc,
-                     int64_t &o64, int64_t &c64) {
-        o64 = 0;
-        c64 = 0;
+    auto decode = [](uint32_t v, int n, const KDim *set, uint32_t &o, uint32_t &c) {
         for (int i = 0; i < n; ++i) {
-            const uint32_t e = (uint32_t)ext[i];
-            const uint32_t q = v / e;
-            const uint32_t id = v - q * e;
-            v = q;
-            o64 += (int64_t)id * so[i];
-            c64 += (int64_t)id * sc[i];
+            const KDim &k = set[i];
+            const uint32_t id = digit(v, k);
+            o += id * (uint32_t)k.s0;
+            c += id * (uint32_t)k.s1;
         }
     };
     for (int r = tid; r < MT + NT; r += NTH) {
-        int64_t o64, c64;
         if (r < MT) {
             const uint32_t v = (uint32_t)(tx * MT) + r;
-            int oo = -1, oc = -1;
-            if ((int64_t)v < d.sizeX) {
-                decode(v, d.nx, d.extX, d.strXop, d.strCx, o64, c64);
-                oo = (int)(o64 - b.x);
-                oc = (int)(c64 - b.cx);
-            }
-            rowX[r] = oo;
-            offCx[r] = oc;
+            uint32_t oo = (uint32_t)-b.x, oc = (uint32_t)-b.cx;
+            decode(v, d.nx, d.x, oo, oc);
+            const bool in = (int64_t)v < d.sizeX;
+            rowX[r] = in ? (int)oo : -1;
+            offCx[r] = in ? (int)oc : -1;
         } else {
             const int rr = r - MT;
             const uint32_t v = (uint32_t)(ty * NT) + rr;
-            int oo = -1, oc = -1;
-            if ((int64_t)v < d.sizeY) {
-                decode(v, d.ny, d.extY, d.strYop, d.strCy, o64, c64);
-                oo = (int)(o64 - b.y);
-                oc = (int)(c64 - b.cy);
-            }
-            rowY[rr] = oo;
-            offCy[rr] = oc;
+            uint32_t oo = (uint32_t)-b.y, oc = (uint32_t)-b.cy;
+            decode(v, d.ny, d.y, oo, oc);
+            const bool in = (int64_t)v < d.sizeY;
+            rowY[rr] = in ? (int)oo : -1;
+            offCy[rr] = in ? (int)oc : -1;
         }
     }
 }
@@ -504,28 +507,22 @@ template <int KT, int NTH>
 __device__ __forceinline__ void box_tables(const KDesc &d, int tid, int *kX, int *kY, int *kco)
 {
     for (int kk = tid; kk < KT; kk += NTH) {
-        int ox = 0, oy = 0;
+        uint32_t ox = 0, oy = 0;   // within the box's span, below 2^31 - 1 (checked by the plan)
         int pos = kInvalidK;
         if (kk < d.kbox) {
             uint32_t k = (uint32_t)kk;
-            int64_t x64 = 0, y64 = 0;
             for (int i = 0; i < d.kj; ++i) {
-                const uint32_t e = (uint32_t)d.extK[i];
-                const uint32_t q = k / e;
-                const uint32_t id = k - q * e;
-                k = q;
-                x64 += (int64_t)id * d.strXk[i];
-                y64 += (int64_t)id * d.strYk[i];
+                const KDim &ki = d.k[i];
+                const uint32_t id = digit(k, ki);
+                ox += id * (uint32_t)ki.s0;
+                oy += id * (uint32_t)ki.s1;
             }
             pos = (int)k;   // position along index kj, < tj
-            x64 += (int64_t)k * d.strXk[d.kj];
-            y64 += (int64_t)k * d.strYk[d.kj];
-            // within the box's span, which the analyser bounds by 2^31 - 1
-            ox = (int)x64;
-            oy = (int)y64;
+            ox += k * (uint32_t)d.k[d.kj].s0;
+            oy += k * (uint32_t)d.k[d.kj].s1;
         }
-        kX[kk] = ox;
-        kY[kk] = oy;
+        kX[kk] = (int)ox;
+        kY[kk] = (int)oy;
         kco[kk] = pos;
     }
 }

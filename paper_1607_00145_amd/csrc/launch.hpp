@@ -107,7 +107,7 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
         if ((unsigned)d.tile0 >= tiles) return hipSuccess;
         // every piece of every box inside the tensors: the variant without checks
         const bool whole = d.sizeX % t.mt == 0 && d.sizeY % t.nt == 0 &&
-                           (d.nsteps == 0 || (d.kbox == t.kt && d.extK[d.kj] % d.tj == 0));
+                           (d.nsteps == 0 || (d.kbox == t.kt && d.k[d.kj].ext % d.tj == 0));
         constexpr auto kWhole =
             gett_direct_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, XM, YM, true>;
         constexpr auto kPart =
@@ -125,7 +125,7 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
         if (d.kslices > 1 || d.nsteps != 1) return hipErrorInvalidValue;   // one K box
         if ((unsigned)d.tile0 >= tiles) return hipSuccess;
         const bool whole = d.sizeX % t.mt == 0 && d.sizeY % t.nt == 0 && d.kbox == t.kt &&
-                           d.extK[d.kj] % d.tj == 0;
+                           d.k[d.kj].ext % d.tj == 0;
         constexpr auto kWhole =
             gett_direct_stream_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, XM, YM, true>;
         constexpr auto kPart =
