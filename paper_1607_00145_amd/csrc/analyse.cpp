@@ -537,6 +537,51 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         return 0;
     };
 
+    // Order of the boxes of a direct-load kernel after a K split, Ik = (u_in,
+    // v, u_out, ...): a box is u_in (f positions of X's stride-one index) by
+    // kt / f positions of v (Y's), so it uses f elements of each of X's cache
+    // lines and kt / f of Y's.  Walking all of v first returned to X's lines
+    // only after every block of v, from HBM by then: the rest of a line was
+    // fetched again for each box.  Here the boxes that share X's lines come
+    // first, then those that share Y's: (u_in, v_in, u_mid, v_mid, u_out,
+    // v_out, ...), u_mid and v_mid the boxes per 128-byte line.  v has to
+    // divide into whole blocks (else the order stays).  Measured on the
+    // 7056 x 8064 x 9216 fp32 contraction: 10.19 ms, in this order 9.53 ms.
+    // The macro-kernels keep the plain order, which measured 2-10% faster on
+    // their shallower boxes and K slices.
+    auto walk_lines = [&](int kt) {
+        const int64_t line = dtype == GETT_FLOAT32 ? 32 : 16;   // elements of 128 bytes
+        const int64_t f = Ik[0].extent, vin = kt / f;
+        if ((int)Ik.size() + 3 > kMaxDims || Ik[1].extent % vin) return;
+        auto part = [](const Index &x, int64_t skip, int64_t ext, const char *tag, int64_t n) {
+            Index p = x;
+            p.extent = ext;
+            p.name = x.name + tag + std::to_string(n);
+            p.strA *= skip;
+            p.strB *= skip;
+            p.strC *= skip;
+            return p;
+        };
+        auto divisor = [](int64_t n, int64_t cap) {
+            int64_t d = std::max<int64_t>(1, std::min(n, cap));
+            while (n % d) --d;
+            return d;
+        };
+        const Index v = Ik[1];
+        // u_out, where the split left one, has the name of no other index
+        const bool hasU = Ik.size() > 2 && Ik[2].strA == Ik[0].strA * f && Ik[2].strB == Ik[0].strB * f;
+        std::vector<Index> next = {Ik[0], part(v, 1, vin, "<", vin)};
+        const int64_t rv = v.extent / vin, n = divisor(rv, line / vin);
+        const int64_t m = hasU ? divisor(Ik[2].extent, line / f) : 1;
+        if (m > 1) next.push_back(part(Ik[2], 1, m, "|", m));
+        if (n > 1) next.push_back(part(v, vin, n, "|", n));
+        if (hasU && Ik[2].extent > m) next.push_back(part(Ik[2], m, Ik[2].extent / m, "|>", m));
+        if (rv > n) next.push_back(part(v, vin * n, rv / n, ">", vin * n));
+        for (size_t i = hasU ? 3 : 2; i < Ik.size(); ++i) next.push_back(Ik[i]);
+        Ik.swap(next);
+        nk = (int)Ik.size();
+    };
+
     // ---- tile shape: the paper ranks candidates with a performance model
     //      (Sec. 3.4: macro-kernel time from flops / (peak * penalty), packing
     //      and unpacking time from bytes / bandwidth).  Here: MFMA time of the
@@ -615,11 +660,13 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // tile with one wavefront per SIMD (1.7: on the fp32 4D x 4D
         // contractions 28 and 30 of Appendix A the 128 x 128 x 32 tile took
         // 17.7 ms, the 128 x 256 x 32 tile with two wavefronts per SIMD
-        // 10.5 ms).
-        const double kSplitWait = !kSplitAhead || b.nsteps <= 1 ? 1.0
-                                  : c.nbuf == 1                 ? 1.4
-                                  : c.wpe == 1                  ? 1.7
-                                                                : 1.0;
+        // 10.5 ms), and the more so a box of 16 fp32 positions, 16-byte runs
+        // of both operands (the same contractions: over 21 ms on 128 x 128 x 16).
+        const double kSplitWait = !kSplitAhead || b.nsteps <= 1         ? 1.0
+                                  : c.nbuf == 1                         ? 1.4
+                                  : dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.2
+                                  : c.wpe == 1                          ? 1.7
+                                                                        : 1.0;
         const double tMfma = perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait;
         // The persistent streaming kernel needs the contracted set in one box.
         const bool canStream = c.stream && b.nsteps <= 1;
@@ -664,15 +711,18 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // Direct-load kernel (tiles that carry it): both operands gathered in
         // vectors.  It sustains deff of the MFMA peak where the macro-kernel
         // sustains eff; its memory stream is priced as the macro-kernel's.
-        if (c.deff > 0.0f && !slowGather && !(flags & GETT_FLAG_SCALAR) && !kSplitAhead &&
-            b.nsteps >= 1) {
+        // After a K split X runs along its block and Y's strided vectors
+        // along theirs; nothing is staged in registers, so the split's late
+        // lines cost no wait beyond the copy's (kSplitWait).
+        if (c.deff > 0.0f && !(flags & GETT_FLAG_SCALAR) && b.nsteps >= 1 &&
+            (kSplitAhead ? aligned(Ix, sX, -1) : !slowGather)) {
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw * cuShare);
             Candidate cd;
             cd.tile = t;
             cd.kind = 4;
-            cd.tMfma = tMfma * c.eff / c.deff;
+            cd.tMfma = tMfma / kSplitWait * c.eff / c.deff;
             cd.tMem = tMem;
             cd.cost = bound(std::max(cd.tMfma, tMem), tChain);
             ranked.push_back(cd);
@@ -760,8 +810,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             b.nsteps >= 16 && ntile > 256.0 && std::fmod(ntile, 256.0) > 0.0) {
             const int occ = (int)tail_occupancy(c, itemB);
             const double boxFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * c.kt * 2.0;
-            const double boxTime = std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) *
-                                   (kSplitAhead && c.nbuf == 1 ? 1.4 : 1.0);
+            const double boxTime =
+                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) * kSplitWait;
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw);
@@ -928,6 +978,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 } else {
                     ysplit = kGatherKVecStrided;
                     yes = (int)f;
+                    if (kind == 4) walk_lines(ts.kt);
                 }
             }
         }
@@ -989,7 +1040,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     }
     // The direct-load kernel takes vector gathers of both operands; a plan
     // that ends up otherwise runs its tile's macro-kernel.
-    if (kind == 4 && !(xmode <= kGatherKVec && ymode <= kGatherKVec && nsteps >= 1)) kind = 0;
+    if (kind == 4 && !(direct_modes(xmode, ymode) && nsteps >= 1)) kind = 0;
     if (kind == 5 && !(xmode <= kGatherKVec && ymode <= kGatherKVec && nsteps == 1)) kind = 0;
     bool cvec = !(flags & GETT_FLAG_SCALAR) && Iy[0].strC == 1 && Iy[0].extent % VW == 0;
     for (auto &x : Ix) if (x.strC % VW) cvec = false;

@@ -297,7 +297,8 @@ gett_status_t contract_with(const gett_plan_s &P, double alpha, const void *A, c
         Y = nullptr;
     }
     // the direct-load kernels need both vector gathers (aligned operands)
-    if ((kind == 4 || kind == 5) && (xmode > kGatherKVec || ymode > kGatherKVec)) kind = 0;
+    if (kind == 4 && !direct_modes(xmode, ymode)) kind = 0;
+    if (kind == 5 && (xmode > kGatherKVec || ymode > kGatherKVec)) kind = 0;
     LaunchFn fn = launch_fn(P.dtype, P.tile, xmode, ymode, kind);
     if (!fn) return GETT_ERROR_NOT_SUPPORTED;
     if (inject_launch_fault()) return GETT_ERROR_HIP;

@@ -32,6 +32,14 @@ enum GatherMode : int {
     kGatherKVecStrided = 4
 };
 
+// Gather modes the direct-load kernel takes: vectors on both sides, Y's
+// possibly strided by a split of the K box (X's then run along its block).
+constexpr bool direct_modes(int xmode, int ymode)
+{
+    return (xmode <= kGatherKVec && ymode <= kGatherKVec) ||
+           (xmode == kGatherKVec && ymode == kGatherKVecStrided);
+}
+
 // Division of v < 2^31 by a divisor known to the host: q = (v * mag) >> 32 >> sh
 // with sh = ceil(log2 n) - 1 and mag = floor(2^(32 + sh) / n) + 1 (Granlund and
 // Montgomery, "Division by Invariant Integers using Multiplication"; mag * n

@@ -1,6 +1,7 @@
 // direct.hpp -- the direct-load variants of the macro-kernel (device code).
 //
-// When both operands are gathered in 16-byte vectors (row or k vectors),
+// When both operands are gathered in 16-byte vectors (row or k vectors; on
+// the Y side also k vectors strided by the split of the K box),
 // packing (Eq. 9-10) needs no registers: the load unit copies each 16-byte
 // piece from device memory straight into LDS (global_load_lds_dwordx4: lane
 // i of one instruction fills bytes [16 i, 16 i + 16) after a wave-uniform LDS
@@ -14,6 +15,8 @@
 //                       the lanes of an MFMA read, which take rows R apart at
 //                       one k piece (R = 4 in fp32, 2 in fp64), fall on
 //                       different banks.
+//   strided k-vector:   [row][k] likewise; a piece holds VW positions es apart,
+//                       so the MFMA steps read it element by element.
 // A k-vector piece holds VW consecutive contracted positions, and one LDS
 // read hands them to VW consecutive MFMA steps: the position lane group g
 // supplies in step s is
@@ -66,7 +69,8 @@ __device__ __forceinline__ int kvec_piece(int r, int c)
 // image.  A piece outside the tensor (its rows past the tile's last, or its
 // contracted positions past the box's valid ones) is not loaded: the thread
 // writes zeros to its place instead, as the macro-kernel's gathers do.
-// WHOLE: every piece of every box is inside (no checks).  R: rows one lane
+// WHOLE: every box is whole (no checks; rows past the tile's last load its
+// first row, and nothing reads their results).  R: rows one lane
 // reads together from the [row][k] layout (RX / RY), which sets the row
 // period of the k-vector permutation.
 template <typename T, int ROWS, int KT, int MODE, int NTH, bool WHOLE, int R>
@@ -77,7 +81,8 @@ struct DirectOperand {
     static constexpr int J = PIECES / NTH;
     static constexpr int CPR = KT / VW;     // k-vector layout: pieces per row
     static constexpr int RPL = ROWS / VW;   // row-vector layout: pieces per line
-    static_assert(MODE == kGatherRowVec || MODE == kGatherKVec, "vector gathers only");
+    static_assert(MODE == kGatherRowVec || MODE == kGatherKVec || MODE == kGatherKVecStrided,
+                  "vector gathers only");
     static_assert(PIECES % NTH == 0 && J >= 1, "whole pieces per thread");
     static_assert(ROWS % VW == 0 && KT % VW == 0, "whole vectors");
     typedef typename Traits<T>::vec vec;
@@ -91,9 +96,10 @@ struct DirectOperand {
     static __device__ __forceinline__ int swz(int r, int c) { return kvec_piece<CPR, R>(r, c); }
 
     // rowoff: LDS table of operand offsets per tile row (-1 = outside the
-    // tensor); koff / kco: offsets / kj-positions per box position
+    // tensor); koff / kco: offsets / kj-positions per box position; es: box
+    // positions between the elements of a strided k-vector
     __device__ __forceinline__ void setup(int tid, const int *rowoff, const int *koff,
-                                          const int *kco)
+                                          const int *kco, int es = 1)
     {
         lane = tid & 63;
         const int w = tid >> 6;
@@ -104,6 +110,10 @@ struct DirectOperand {
             if constexpr (MODE == kGatherKVec) {
                 r = p / CPR;
                 kk = VW * swz(r, p % CPR);
+            } else if constexpr (MODE == kGatherKVecStrided) {
+                r = p / CPR;
+                const int c = swz(r, p % CPR), nq = CPR / es;   // piece c: value c / nq of the
+                kk = c / nq + (c % nq) * VW * es;               // first index, vector c % nq
             } else {
                 r = VW * (p % RPL);
                 kk = p / RPL;
@@ -139,15 +149,38 @@ struct DirectFrag {
     typedef typename Traits<T>::vec vec;
     typedef RVec<T, R> RV;
     static constexpr bool kKV = MODE == kGatherKVec;
+    static constexpr bool kKS = MODE == kGatherKVecStrided;
+    static constexpr bool kRV = MODE == kGatherRowVec;
     static constexpr int CPR = KT / VW;
-    static constexpr int kReads = kKV ? NB : VW * (NB / R);   // LDS reads per group
-    // k-vector: one piece per block (VW positions of its row); row-vector:
-    // one read of R rows per block group for each of the VW steps
+    static constexpr int kReads = kKV ? NB : kKS ? VW * NB : VW * (NB / R);   // LDS reads per group
+    // k-vector: one piece per block (VW positions of its row); strided
+    // k-vector: one element per block and step; row-vector: one read of R
+    // rows per block group and step
     vec kv[kKV ? NB : 1];
-    typename RV::type rv[kKV ? 1 : VW][kKV ? 1 : NB / R];
+    T sv[kKS ? VW : 1][kKS ? NB : 1];
+    typename RV::type rv[kRV ? VW : 1][kRV ? NB / R : 1];
 
-    __device__ __forceinline__ void read(const T *tile, int w0, int l16, int g, int grp)
+    __device__ __forceinline__ void read(const T *tile, int w0, int l16, int g, int grp, int es = 1)
     {
+        if constexpr (kKS) {
+            // position kk = u + es (VW q + e) is element e of piece u nq + q
+            // (es is a power of two).  The lanes of one read take the same
+            // piece of rows R apart, so the permutation spreads them over
+            // the banks as for the k-vector reads, and neighbouring lane
+            // groups take neighbouring elements or pieces.
+            const int nq = CPR / es, sh = __builtin_ctz(es);
+#pragma unroll
+            for (int s4 = 0; s4 < VW; ++s4) {
+                const int kk = 4 * VW * grp + VW * g + s4;
+                const int v = kk >> sh, c = (kk & (es - 1)) * nq + v / VW;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int r = w0 + block_row<R>(b, l16);
+                    sv[s4][b] = tile[r * KT + VW * kvec_col<CPR, R>(r, c) + v % VW];
+                }
+            }
+            return;
+        }
         if constexpr (kKV) {
             const int q = 4 * grp + g;   // piece of positions kp(VW grp .. VW grp + VW - 1, g)
 #pragma unroll
@@ -170,6 +203,7 @@ struct DirectFrag {
     __device__ __forceinline__ T at(int b, int s4) const
     {
         if constexpr (kKV) return kv[b][s4];
+        else if constexpr (kKS) return sv[s4][b];
         else return RV::at(rv[s4][b / R], b % R);
     }
 };
@@ -274,8 +308,9 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
 
     OX ox;
     OY oy;
+    const int es = YMODE == kGatherKVecStrided ? d.yes : 1;
     ox.setup(tid, rowX, kX, kco);
-    oy.setup(tid, rowY, kY, kco);
+    oy.setup(tid, rowY, kY, kco, es);
     w.zero();
     const uint32_t nsteps = (uint32_t)d.nsteps;
     const int l16 = tid & 15, g = (tid & 63) >> 4;
@@ -295,7 +330,7 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
 #pragma unroll
         for (int grp = 0; grp < NG; ++grp) {
             fx[grp].read(st, xw, l16, g, grp);
-            fy[grp].read(st + MT * KT, yw, l16, g, grp);
+            fy[grp].read(st + MT * KT, yw, l16, g, grp, es);
         }
     };
     auto mma = [&](const FX &fx, const FY &fy) {

@@ -105,9 +105,12 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
     } else if constexpr (KIND == 4) {
         if (d.kslices > 1) return hipErrorInvalidValue;   // whole tiles only
         if ((unsigned)d.tile0 >= tiles) return hipSuccess;
-        // every piece of every box inside the tensors: the variant without checks
-        const bool whole = d.sizeX % t.mt == 0 && d.sizeY % t.nt == 0 &&
-                           (d.nsteps == 0 || (d.kbox == t.kt && d.k[d.kj].ext % d.tj == 0));
+        // every box whole: the variant without checks.  Rows past the last of
+        // a ragged tile then load the tile's first row (an element of the
+        // tensor) into panel rows whose results are not stored; only
+        // positions past a partial box have to be zeros.  Checking the rows
+        // too cost ragged shapes 5-6% (6144 x 3840 x 9216 fp32: 3.46 ms).
+        const bool whole = d.nsteps == 0 || (d.kbox == t.kt && d.k[d.kj].ext % d.tj == 0);
         constexpr auto kWhole =
             gett_direct_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, XM, YM, true>;
         constexpr auto kPart =
@@ -162,7 +165,7 @@ LaunchFn pick_modes(int xm, int ym, int kind)
     constexpr bool kDStream = TileTable<T>::tiles[TI].dsbw > 0.0f;
 #define GETT_CASE(a, b)                                                                       \
     if (xm == a && ym == b) {                                                                 \
-        constexpr bool kDir = kDirect && a <= 1 && b <= 1;   /* vector gathers only */       \
+        constexpr bool kDir = kDirect && direct_modes(a, b);                                  \
         if (kind == 0) return &launch_one<T, TI, a, b, 0>;                                   \
         if (kind == 2) return &launch_one<T, TI, a, b, 2>;                                   \
         if (kind == 1 && kStream) return &launch_one<T, TI, a, b, kStream ? 1 : 0>;          \
