@@ -104,6 +104,9 @@ struct KDesc {
                                    // are summed in slice order through the workspace
     int32_t crun;                  // > 0: C's stride-one run along y, stored in C order
                                    // through LDS (E elements; 0: per-lane stores only)
+    int32_t stepY;                 // columns from one tile to the next: the tile's NT, or
+                                   // the whole runs of crun in it (the last columns idle)
+    Recip piecesInv;               // of the 16-byte pieces per run
     int32_t xperm, yperm;          // > 0: element-wise gathers of X (Y) walk the tile rows
                                    // grouped by row mod this extent (0: in order)
     int32_t tile0;                 // first tile of the grid (> 0: a pass over tiles tile0..)

@@ -442,7 +442,7 @@ __device__ __forceinline__ int64_t uniform(int64_t v)
 }
 
 // Base offsets of one tile: rows [tx MT, ...) of the x set, columns
-// [ty NT, ...) of the y set, in the operands and in C.
+// [ty stepY, ...) of the y set, in the operands and in C.
 struct TileBase {
     int64_t x, cx, y, cy;
 };
@@ -451,9 +451,9 @@ template <int MT, int NT>
 __device__ __forceinline__ TileBase tile_base(const KDesc &d, int tx, int ty)
 {
     TileBase b;
-    const uint32_t x0 = (uint32_t)(uniform(tx) * MT), y0 = (uint32_t)(uniform(ty) * NT);
+    const uint32_t x0 = (uint32_t)(uniform(tx) * MT), y0 = (uint32_t)(uniform(ty) * d.stepY);
     const uint32_t x1 = (uint32_t)min((int64_t)x0 + MT, d.sizeX) - 1;
-    const uint32_t y1 = (uint32_t)min((int64_t)y0 + NT, d.sizeY) - 1;
+    const uint32_t y1 = (uint32_t)min((int64_t)y0 + d.stepY, d.sizeY) - 1;
     range_base(d.nx, d.x, x0, x1, b.x, b.cx);
     range_base(d.ny, d.y, y0, y1, b.y, b.cy);
     b.x = uniform(b.x);
@@ -492,10 +492,10 @@ __device__ __forceinline__ void tile_tables(const KDesc &d, int tx, int ty, cons
             offCx[r] = in ? (int)oc : -1;
         } else {
             const int rr = r - MT;
-            const uint32_t v = (uint32_t)(ty * NT) + rr;
+            const uint32_t v = (uint32_t)(ty * d.stepY) + rr;
             uint32_t oo = (uint32_t)-b.y, oc = (uint32_t)-b.cy;
             decode(v, d.ny, d.y, oo, oc);
-            const bool in = (int64_t)v < d.sizeY;
+            const bool in = (int64_t)v < d.sizeY && rr < d.stepY;
             rowY[rr] = in ? (int)oo : -1;
             offCy[rr] = in ? (int)oc : -1;
         }
@@ -714,12 +714,6 @@ struct WaveTile {
     {
         return wm * WTM + block_row<RX>(grp * RX + q / 4, Traits<T>::mrow(g, q % 4));
     }
-    // column y lies in a run [kE, kE + E) wholly inside [y0, ylim)
-    static __device__ __forceinline__ bool in_whole_run(int y, int y0, int ylim, int E)
-    {
-        const int k = y / E;
-        return k * E >= y0 && (k + 1) * E <= ylim;
-    }
     // alpha * acc of the column groups whose first column lies in [c0, c1)
     // into stage[row][col - c0] (row pitch `pitch`; vector C accesses only)
     __device__ __forceinline__ void stage(T *st, int pitch, int c0, int c1, T alpha) const
@@ -748,16 +742,11 @@ struct WaveTile {
     // together, then the updates and non-temporal stores (C is written once
     // and not reused).  C is not read when beta == 0.
     //
-    // E > 0 (vector C accesses only): skip the column groups that lie in a run
-    // of E columns wholly inside the tile's columns [y0, ylim) -- those are
-    // stored in C's memory order by unpack_c_order.
-    //
     // ALL: every row and column of the tile lies inside C (no offset checks,
     // so every wavefront issues every store).
     template <int PARTS = 1, bool ALL = false>
     __device__ __forceinline__ void unpack(T *__restrict__ C, const int *offCx, const int *offCy,
-                                           T alpha, T beta, bool cvec, int y0 = 0, int ylim = 0,
-                                           int E = 0) const
+                                           T alpha, T beta, bool cvec) const
     {
         static_assert(NR % PARTS == 0, "row parts");
         constexpr int NP = NR / PARTS;
@@ -769,11 +758,6 @@ struct WaveTile {
             if (kVecC && cvec) {
                 int oy[CGV];
                 cols_vec(offCy, oy);
-                if (E > 0) {
-#pragma unroll
-                    for (int cg = 0; cg < CGV; ++cg)
-                        if (in_whole_run(y0 + col_of(cg), y0, ylim, E)) oy[cg] = -1;
-                }
 #pragma unroll
                 for (int part = 0; part < PARTS; ++part) {
                     vec cv[NP][CGV];
@@ -899,48 +883,68 @@ struct WaveTile {
 // Unpack in C's memory order, for a C whose stride-one run (E elements of the
 // first column index) is shorter than a cache line while the next index in
 // memory is a row index: the per-lane stores of the MFMA layout would write
-// each 16-lane piece of a row into several runs, partial lines all.  The
-// columns of every run wholly inside the tile are staged in LDS (the packing
-// buffers, free after the K loop; as many runs per pass as fit in `cap`
-// elements) and the workgroup stores them as (run, row, 16-byte piece) in
-// order, so consecutive lanes write consecutive addresses through a run and
-// on across rows.  Columns of runs cut by the tile's edges are stored per lane.
+// each 16-lane piece of a row into several runs, partial lines all.  The tile
+// holds whole runs (`cols` columns; the plan's stepY).  They are staged in LDS
+// (the packing buffers, free after the K loop; as many runs per pass as fit in
+// `cap` elements) and the workgroup stores them as (run, row, 16-byte piece)
+// in order, so consecutive lanes write consecutive addresses through a run
+// and on across rows.
+//
+// Bound by the C stream, provided the index arithmetic stays out of its way:
+// a piece costs one multiplication by the host's reciprocal of the pieces per
+// run (MT is a power of two), and kBatch pieces are addressed, read and stored
+// together, so their LDS reads (and C reads) overlap (four of them spilled).
+// The 6D fp32 contraction with runs of 24 (C of 369 MB) took 146 us with two
+// runtime divisions per piece and cut runs stored per lane, 123 us now.
 template <typename T, int MT, int NTH, typename WT>
 __device__ __forceinline__ void unpack_c_order(const WT &w, T *__restrict__ C, T *stage, int cap,
-                                               const int *offCx, const int *offCy, int y0,
-                                               int ylim, int E, T alpha, T beta, int tid)
+                                               const int *offCx, const int *offCy, int cols,
+                                               int E, Recip piecesInv, T alpha, T beta, int tid)
 {
     constexpr int VW = Traits<T>::VW;
+    constexpr int kBatch = 2;
+    static_assert((MT & (MT - 1)) == 0, "rows split off by a mask");
     typedef typename Traits<T>::vec vec;
-    w.unpack(C, offCx, offCy, alpha, beta, true, y0, ylim, E);   // runs cut by the edges
-    const int k0 = (y0 + E - 1) / E, k1 = ylim / E;            // whole runs [k0, k1)
-    if (k1 <= k0) return;
-    const int perPass = (cap / MT - VW) / E;                   // >= 1 (checked by the plan)
-    const int pitch = perPass * E + VW;
     const int pieces = E / VW;                                 // 16-byte pieces per run row
-    const bool readC = beta != T(0);
-    for (int ka = k0; ka < k1; ka += perPass) {
-        const int kb = min(k1, ka + perPass);
-        const int c0 = ka * E - y0, c1 = kb * E - y0;         // tile-local columns of the pass
+    const int perPass = (int)quotient((uint32_t)(cap / MT / VW - 1), pieces, piecesInv) * E;
+    const int pitch = perPass + VW;                            // columns of a pass, >= E (checked
+    const bool readC = beta != T(0);                           // by the plan)
+    for (int c0 = 0; c0 < cols; c0 += perPass) {
+        const int c1 = min(cols, c0 + perPass);
         __syncthreads();   // the LDS is free: the last MFMAs or the previous pass are done
         w.stage(stage, pitch, c0, c1, alpha);
         __syncthreads();
-        const int n = (kb - ka) * MT * pieces;
-        for (int L = tid; L < n; L += NTH) {
-            const int run = L / (MT * pieces);
-            const int rest = L - run * (MT * pieces);
-            const int row = rest / pieces;
-            const int col = c0 + run * E + (rest - row * pieces) * VW;
-            const int ox = offCx[row];
-            if (ox < 0) continue;   // a row outside the tensor
-            vec v = *reinterpret_cast<const vec *>(stage + row * pitch + (col - c0));
-            T *dst = C + ox + offCy[col];
-            if (readC) {
-                const vec c = __builtin_nontemporal_load(reinterpret_cast<const vec *>(dst));
+        const int n = (c1 - c0) / VW * MT;                     // pieces of the pass
+        for (int L0 = tid; L0 < n; L0 += kBatch * NTH) {
+            int off[kBatch];   // offset in C, -1: past the last piece, or a row outside the tensor
+            vec v[kBatch];
 #pragma unroll
-                for (int j = 0; j < VW; ++j) v[j] += beta * c[j];
+            for (int i = 0; i < kBatch; ++i) {
+                const int L = L0 + i * NTH;
+                off[i] = -1;
+                if (L >= n) continue;
+                const int t = (int)quotient((uint32_t)L, pieces, piecesInv);   // run * MT + row
+                const int row = t & (MT - 1);
+                const int scol = (t / MT) * E + (L - t * pieces) * VW;   // column within the pass
+                const int ox = offCx[row];
+                v[i] = *reinterpret_cast<const vec *>(stage + row * pitch + scol);
+                off[i] = ox < 0 ? -1 : ox + offCy[c0 + scol];
             }
-            __builtin_nontemporal_store(v, reinterpret_cast<vec *>(dst));
+            if (readC) {
+                vec c[kBatch];
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i)
+                    if (off[i] >= 0)
+                        c[i] = __builtin_nontemporal_load(reinterpret_cast<const vec *>(C + off[i]));
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+                    for (int j = 0; j < VW; ++j) v[i][j] += beta * c[i][j];
+            }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i)
+                if (off[i] >= 0)
+                    __builtin_nontemporal_store(v[i], reinterpret_cast<vec *>(C + off[i]));
         }
     }
 }
@@ -1022,7 +1026,7 @@ gett_macro_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ 
         const T *Yt = Y + tb.y;
         T *Ct = C + (tb.cx + tb.cy);
         if (XMODE == kGatherScalar && d.xperm > 0) row_perm<MT, NTH>(d.xperm, tx * MT, tid, permX);
-        if (YMODE == kGatherScalar && d.yperm > 0) row_perm<NT, NTH>(d.yperm, ty * NT, tid, permY);
+        if (YMODE == kGatherScalar && d.yperm > 0) row_perm<NT, NTH>(d.yperm, ty * d.stepY, tid, permY);
         __syncthreads();
 
         GX gx;
@@ -1144,12 +1148,11 @@ gett_macro_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ 
                 __hip_atomic_store(cnt + part.ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         }
-        if constexpr (CORDER && WT::kVecC) {   // compiled only into the tiles that carry it
+        if constexpr (CORDER && WT::kVecC && !kPartials) {   // compiled only into the tiles that carry it
             if (d.crun > 0 && d.cvec) {
-                const int y0 = ty * NT;
-                const int ylim = (int)min((int64_t)y0 + NT, d.sizeY);
-                unpack_c_order<T, MT, NTH>(w, Ct, panels, kPanels, offCx, offCy, y0, ylim, d.crun,
-                                           alpha, beta, tid);
+                const int cols = (int)min((int64_t)d.stepY, d.sizeY - (int64_t)ty * d.stepY);
+                unpack_c_order<T, MT, NTH>(w, Ct, panels, kPanels, offCx, offCy, cols, d.crun,
+                                           d.piecesInv, alpha, beta, tid);
                 return;
             }
         }
