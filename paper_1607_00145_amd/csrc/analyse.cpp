@@ -1111,13 +1111,12 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     d.sizeY = sizeY;
     d.nx = (int)Ix.size();
     d.ny = (int)Iy.size();
-    for (int i = 0; i < d.nx; ++i)
-        d.x[i] = dim(Ix[i].extent, sX(Ix[i]), Ix[i].strC);
-    for (int i = 0; i < d.ny; ++i)
-        d.y[i] = dim(Iy[i].extent, sY(Iy[i]), Iy[i].strC);
     d.nk = nk;
-    for (int i = 0; i < nk; ++i)
-        d.k[i] = dim(Ik[i].extent, sX(Ik[i]), sY(Ik[i]));
+    if (d.nx + d.ny + d.nk > kMaxIndices) return GETT_ERROR_NOT_SUPPORTED;   // cannot happen
+    KDim *at = d.dim;
+    for (const Index &i : Ix) *at++ = dim(i.extent, sX(i), i.strC);
+    for (const Index &i : Iy) *at++ = dim(i.extent, sY(i), i.strC);
+    for (const Index &i : Ik) *at++ = dim(i.extent, sX(i), sY(i));
     d.kj = kj;
     d.tj = (int32_t)tj;
     d.kbox = (int32_t)kbox;

@@ -14,9 +14,17 @@
 #pragma once
 #include <stdint.h>
 
+#ifndef __HIP__
+#define __host__
+#define __device__
+#endif
+
 namespace gett {
 
 constexpr int kMaxDims = 16;   // per index set (== GETT_MAX_RANK)
+// Indices of the three sets together: each is in two of the three tensors
+// (3 x 16 / 2), an empty set adds one, a split of one set up to four.
+constexpr int kMaxIndices = 30;
 
 // Gather modes of an operand tile (see kernel.hpp).
 enum GatherMode : int {
@@ -76,11 +84,8 @@ struct KDesc {
     int64_t sizeX;                 // S_{I_x}
     int64_t sizeY;                 // S_{I_y}
     int32_t nx, ny;                // number of (merged) indices in each set
-    KDim x[kMaxDims];              // first = fastest in the linear order; s0: X, s1: C
-    KDim y[kMaxDims];              // s0: Y, s1: C
     // ---- contracted set, walked as K boxes ----
     int32_t nk;                    // number of (merged) contracted indices (>= 1)
-    KDim k[kMaxDims];              // s0: X, s1: Y
     int32_t kj;                    // index that is blocked (earlier ones are whole)
     int32_t tj;                    // block length along index kj
     int32_t kbox;                  // elements in one box = prod(earlier extents) * tj
@@ -114,6 +119,13 @@ struct KDesc {
     int32_t tailFull;              // tiles computed whole, one workgroup each
     int32_t tailWgs;               // workgroups that share the boxes of the other tiles
     int32_t tailLen;               // boxes per such workgroup
+    // ---- the indices, one set after the other (first = fastest in the set's
+    //      linear order): a kernel finds them in the first few cache lines of
+    //      its arguments, and a launch copies no more than it has to ----
+    KDim dim[kMaxIndices];
+    __host__ __device__ const KDim *x() const { return dim; }            // s0: X, s1: C
+    __host__ __device__ const KDim *y() const { return dim + nx; }       // s0: Y, s1: C
+    __host__ __device__ const KDim *k() const { return dim + nx + ny; }  // s0: X, s1: Y
 };
 
 }  // namespace gett

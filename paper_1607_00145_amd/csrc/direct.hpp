@@ -223,16 +223,16 @@ struct DirectWalk {
 
     __device__ __forceinline__ void init(const KDesc &d)
     {
-        const KDim &kj = d.k[d.kj];
+        const KDim &kj = d.k()[d.kj];
         nblk = d.nblk > 0 ? d.nblk : 1;
         ek = kj.ext;
         tj = d.tj;
         bx = (int64_t)d.tj * kj.s0;
         by = (int64_t)d.tj * kj.s1;
         const bool later = d.kj + 1 < d.nk;
-        e1 = later ? d.k[d.kj + 1].ext : 0;
-        sx1 = later ? d.k[d.kj + 1].s0 : 0;
-        sy1 = later ? d.k[d.kj + 1].s1 : 0;
+        e1 = later ? d.k()[d.kj + 1].ext : 0;
+        sx1 = later ? d.k()[d.kj + 1].s0 : 0;
+        sy1 = later ? d.k()[d.kj + 1].s1 : 0;
         next = 0;
         blk = 0;
         c1 = 0;
@@ -293,6 +293,7 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
 
     const int tid = (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    touch_arguments();
     const int ntiles = d.tilesX * d.tilesY;
     box_tables<KT, NTH>(d, tid, kX, kY, kco);
     WT w;

@@ -89,6 +89,20 @@ __device__ __forceinline__ uint32_t digit(uint32_t &v, const KDim &i)
     return c;
 }
 
+// Fetch the first cache lines of the kernel's arguments (the descriptor and
+// its first eight indices) in one round trip: the tables read them one index
+// after the other, and a line no workgroup has read yet comes from memory.
+__device__ __forceinline__ void touch_arguments()
+{
+    typedef const __attribute__((address_space(4))) uint32_t *args;
+    const args a = (args)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = a[16 * i];
+    asm volatile("" ::"s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]), "s"(v[5]), "s"(v[6]),
+                 "s"(v[7]));
+}
+
 // Map the hardware workgroup id to a tile.  Workgroups are dealt round-robin
 // to the 8 XCDs (each with its own L2); renumber so that consecutive logical
 // tiles run on one XCD.  Then either walk tiles in bands of `group` x-tiles,
@@ -121,13 +135,13 @@ __device__ __forceinline__ void tile_of_block(const KDesc &d, int bid, int nwg, 
 // valid positions left along index kj.
 __device__ __forceinline__ int box_origin(const KDesc &d, uint32_t s, int64_t &ox, int64_t &oy)
 {
-    const KDim &kj = d.k[d.kj];
+    const KDim &kj = d.k()[d.kj];
     uint32_t rest = quotient(s, d.nblk, d.nblkInv);
     const int blk = (int)(s - rest * (uint32_t)d.nblk);
     ox = (int64_t)(blk * d.tj) * kj.s0;
     oy = (int64_t)(blk * d.tj) * kj.s1;
     for (int i = d.kj + 1; i < d.nk; ++i) {
-        const KDim &k = d.k[i];
+        const KDim &k = d.k()[i];
         const uint32_t c = digit(rest, k);
         ox += (int64_t)c * k.s0;
         oy += (int64_t)c * k.s1;
@@ -156,20 +170,20 @@ struct BoxWalker {
         lim = box_origin(d, s, ox, oy);
         uint32_t rest = quotient(s, nblk, d.nblkInv);
         blk = (int)(s - rest * (uint32_t)nblk);
-        c1 = e1 > 0 ? (int)digit(rest, d.k[d.kj + 1]) : 0;
+        c1 = e1 > 0 ? (int)digit(rest, d.k()[d.kj + 1]) : 0;
     }
     __device__ __forceinline__ void init(const KDesc &d, uint32_t s)
     {
-        const KDim &kj = d.k[d.kj];
+        const KDim &kj = d.k()[d.kj];
         nblk = d.nblk > 0 ? d.nblk : 1;
         tj = d.tj;
         ek = kj.ext;
         bx = (int64_t)d.tj * kj.s0;
         by = (int64_t)d.tj * kj.s1;
         const bool later = d.kj + 1 < d.nk;
-        e1 = later ? d.k[d.kj + 1].ext : 0;
-        sx1 = later ? d.k[d.kj + 1].s0 : 0;
-        sy1 = later ? d.k[d.kj + 1].s1 : 0;
+        e1 = later ? d.k()[d.kj + 1].ext : 0;
+        sx1 = later ? d.k()[d.kj + 1].s0 : 0;
+        sy1 = later ? d.k()[d.kj + 1].s1 : 0;
         reset(d, s);
     }
     // origin of box s (returns the valid positions along kj)
@@ -454,8 +468,8 @@ __device__ __forceinline__ TileBase tile_base(const KDesc &d, int tx, int ty)
     const uint32_t x0 = (uint32_t)(uniform(tx) * MT), y0 = (uint32_t)(uniform(ty) * d.stepY);
     const uint32_t x1 = (uint32_t)min((int64_t)x0 + MT, d.sizeX) - 1;
     const uint32_t y1 = (uint32_t)min((int64_t)y0 + d.stepY, d.sizeY) - 1;
-    range_base(d.nx, d.x, x0, x1, b.x, b.cx);
-    range_base(d.ny, d.y, y0, y1, b.y, b.cy);
+    range_base(d.nx, d.x(), x0, x1, b.x, b.cx);
+    range_base(d.ny, d.y(), y0, y1, b.y, b.cy);
     b.x = uniform(b.x);
     b.cx = uniform(b.cx);
     b.y = uniform(b.y);
@@ -486,7 +500,7 @@ __device__ __forceinline__ void tile_tables(const KDesc &d, int tx, int ty, cons
         if (r < MT) {
             const uint32_t v = (uint32_t)(tx * MT) + r;
             uint32_t oo = (uint32_t)-b.x, oc = (uint32_t)-b.cx;
-            decode(v, d.nx, d.x, oo, oc);
+            decode(v, d.nx, d.x(), oo, oc);
             const bool in = (int64_t)v < d.sizeX;
             rowX[r] = in ? (int)oo : -1;
             offCx[r] = in ? (int)oc : -1;
@@ -494,7 +508,7 @@ __device__ __forceinline__ void tile_tables(const KDesc &d, int tx, int ty, cons
             const int rr = r - MT;
             const uint32_t v = (uint32_t)(ty * d.stepY) + rr;
             uint32_t oo = (uint32_t)-b.y, oc = (uint32_t)-b.cy;
-            decode(v, d.ny, d.y, oo, oc);
+            decode(v, d.ny, d.y(), oo, oc);
             const bool in = (int64_t)v < d.sizeY && rr < d.stepY;
             rowY[rr] = in ? (int)oo : -1;
             offCy[rr] = in ? (int)oc : -1;
@@ -512,14 +526,14 @@ __device__ __forceinline__ void box_tables(const KDesc &d, int tid, int *kX, int
         if (kk < d.kbox) {
             uint32_t k = (uint32_t)kk;
             for (int i = 0; i < d.kj; ++i) {
-                const KDim &ki = d.k[i];
+                const KDim &ki = d.k()[i];
                 const uint32_t id = digit(k, ki);
                 ox += id * (uint32_t)ki.s0;
                 oy += id * (uint32_t)ki.s1;
             }
             pos = (int)k;   // position along index kj, < tj
-            ox += k * (uint32_t)d.k[d.kj].s0;
-            oy += k * (uint32_t)d.k[d.kj].s1;
+            ox += k * (uint32_t)d.k()[d.kj].s0;
+            oy += k * (uint32_t)d.k()[d.kj].s1;
         }
         kX[kk] = (int)ox;
         kY[kk] = (int)oy;
@@ -1007,6 +1021,7 @@ gett_macro_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ 
     __shared__ int zeroLds;     // 0 (see the stream-K tail)
 
     const int tid = (int)threadIdx.x;
+    touch_arguments();
     const int ntiles = d.tilesX * d.tilesY;
     box_tables<KT, NTH>(d, tid, kX, kY, kco);
     WT w;

@@ -110,7 +110,7 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
         // tensor) into panel rows whose results are not stored; only
         // positions past a partial box have to be zeros.  Checking the rows
         // too cost ragged shapes 5-6% (6144 x 3840 x 9216 fp32: 3.46 ms).
-        const bool whole = d.nsteps == 0 || (d.kbox == t.kt && d.k[d.kj].ext % d.tj == 0);
+        const bool whole = d.nsteps == 0 || (d.kbox == t.kt && d.k()[d.kj].ext % d.tj == 0);
         constexpr auto kWhole =
             gett_direct_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, XM, YM, true>;
         constexpr auto kPart =
@@ -128,7 +128,7 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
         if (d.kslices > 1 || d.nsteps != 1) return hipErrorInvalidValue;   // one K box
         if ((unsigned)d.tile0 >= tiles) return hipSuccess;
         const bool whole = d.sizeX % t.mt == 0 && d.sizeY % t.nt == 0 && d.kbox == t.kt &&
-                           d.k[d.kj].ext % d.tj == 0;
+                           d.k()[d.kj].ext % d.tj == 0;
         constexpr auto kWhole =
             gett_direct_stream_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, XM, YM, true>;
         constexpr auto kPart =
