@@ -346,6 +346,19 @@ def _dtype_code(t) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}: float32 or float64 only")
 
 
+def _current_stream() -> int:
+    """The handle of torch's current stream on the current device."""
+    global _current_stream
+    import torch
+    c = torch._C
+    if hasattr(c, "_cuda_getCurrentRawStream") and hasattr(c, "_cuda_getDevice"):
+        raw, device = c._cuda_getCurrentRawStream, c._cuda_getDevice
+        _current_stream = lambda: raw(device())
+    else:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _current_stream()
+
+
 class Plan:
     """A plan bound to the shapes and strides of given torch tensors."""
 
@@ -365,20 +378,28 @@ class Plan:
         if st != 0:
             raise GettError(st, "gett_plan")
         self._h = h
+        self._contract = load_library().gett_contract
 
     def describe(self) -> dict:
         return json.loads(gett_plan_describe(self._h))
 
     def __call__(self, A, B, C, alpha: float = 1.0, beta: float = 0.0, stream=None):
-        import torch
-        for name, t in (("A", A), ("B", B), ("C", C)):
-            if not t.is_cuda:
-                raise ValueError(f"{name} must be a device tensor")
-        if tuple((tuple(t.shape), tuple(t.stride())) for t in (C, A, B)) != self.sig:
+        # One call is a few microseconds of host time, as long as a small
+        # contraction's kernel: shapes and strides are compared as torch hands
+        # them out, the current stream is asked for as a raw handle (a Stream
+        # object costs about 2 us), and the C entry is called through the
+        # function object the plan holds.
+        if not (A.is_cuda and B.is_cuda and C.is_cuda):
+            for name, t in (("A", A), ("B", B), ("C", C)):
+                if not t.is_cuda:
+                    raise ValueError(f"{name} must be a device tensor")
+        (shC, stC), (shA, stA), (shB, stB) = self.sig
+        if (C.shape != shC or A.shape != shA or B.shape != shB or C.stride() != stC or
+                A.stride() != stA or B.stride() != stB):
             raise ValueError("tensor shapes/strides differ from the plan's")
-        s = stream if stream is not None else torch.cuda.current_stream()
-        st = gett_contract(self._h, alpha, A.data_ptr(), B.data_ptr(), beta, C.data_ptr(),
-                           s.cuda_stream)
+        s = _current_stream() if stream is None else stream.cuda_stream
+        st = self._contract(self._h, float(alpha), A.data_ptr(), B.data_ptr(), float(beta),
+                            C.data_ptr(), s)
         if st != 0:
             raise GettError(st, "gett_contract")
         return C
