@@ -221,6 +221,7 @@ const char *kind_name(int k)
            : k == 3 ? "tail"
            : k == 4 ? "direct"
            : k == 5 ? "direct-stream"
+           : k == 6 ? "direct-element"
                     : "macro";
 }
 
@@ -611,6 +612,15 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         return strOf(I[0]) == 1 || strOf(Ik[0]) == 1;
     };
     const bool slowGather = (flags & GETT_FLAG_SCALAR) || !vecable(Ix, sX) || !vecable(Iy, sY);
+    // Whether the operand's extents and strides let it gather in 16-byte
+    // vectors, in the orders as they stand (no split, no C order).
+    auto vectors = [&](const std::vector<Index> &I, auto strOf) {
+        const bool row = strOf(I[0]) == 1 && I[0].extent % VW == 0 && aligned(I, strOf, 0) &&
+                         aligned(Ik, strOf, -1);
+        return !(flags & GETT_FLAG_SCALAR) && (row || (kvec_ok(strOf) && aligned(I, strOf, -1)));
+    };
+    const bool vecX = vectors(Ix, sX), vecY = vectors(Iy, sY);
+    const bool vecC = Iy[0].strC == 1 && Iy[0].extent % VW == 0;
     // Partial tiles (K slices, stream-K tail) are summed through the
     // workspace: the stream of partial tiles and one workgroup's reads of a
     // tile's pieces are priced at these rates (MI355X).
@@ -667,7 +677,29 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                                   : dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.2
                                   : c.wpe == 1                          ? 1.7
                                                                         : 1.0;
-        const double tMfma = perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait;
+        // Element-wise gathers cost an fp32 macro-kernel's one or two
+        // wavefronts per SIMD this much of their MFMA rate (odd extents
+        // against even ones: 4096^3-shaped 1.1-1.25, C of 529 x 3721 over 3721
+        // 1.45 on 32 x 64 tiles).
+        const double kElementWise = dtype != GETT_FLOAT32 || (vecX && vecY) || kSplitAhead ? 1.0
+                                    : c.mt * c.nt <= 32 * 64                               ? 1.3
+                                    : c.wpe == 1                                           ? 1.2
+                                                                                           : 1.1;
+        const double tMfma =
+            perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait * kElementWise;
+        // A tile's offset tables, first gathers and C stores are covered by
+        // nothing when its workgroup has the CU to itself (measured per tile
+        // on fp32 tensors times matrices with contracted sets of 96-384: 4 us
+        // on 128 x 128 macro tiles, 8 us on 128 x 256 direct ones, half of
+        // that for two 128 x 128 direct workgroups; C in single elements
+        // takes two to three times that).
+        const double rounds = std::ceil(tx * ty / 256.0);
+        const double macroSetup = dtype != GETT_FLOAT32      ? 0.0
+                                  : wpt >= 8                 ? rounds * (vecC ? 8.0e-6 : 16.0e-6)
+                                  : c.wpe == 1 && wpt >= 4 ? rounds * (vecC ? 4.0e-6 : 12.0e-6)
+                                                           : 0.0;
+        const double tileSetup =
+            rounds * (vecC ? 8.0e-6 : 16.0e-6) * (wpt >= 8 ? 1.0 : 0.5);
         // The persistent streaming kernel needs the contracted set in one box.
         const bool canStream = c.stream && b.nsteps <= 1;
         // A stream carried by fewer workgroups than CUs gets that share of the
@@ -705,7 +737,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // element-wise gathers into a single LDS buffer (the streaming
             // kernel too) wait with nothing to overlap them, as in the K split
             const double single = (slowGather && (c.nbuf == 1 || k == 1)) ? 1.4 : 1.0;
-            cd.cost = bound(std::max(tMfma, tMem), tChain) * single;
+            cd.cost = bound(std::max(tMfma, tMem), tChain) * single + macroSetup;
             ranked.push_back(cd);
         }
         // Direct-load kernel (tiles that carry it): both operands gathered in
@@ -715,7 +747,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // along theirs; nothing is staged in registers, so the split's late
         // lines cost no wait beyond the copy's (kSplitWait).
         if (c.deff > 0.0f && !(flags & GETT_FLAG_SCALAR) && b.nsteps >= 1 &&
-            (kSplitAhead ? aligned(Ix, sX, -1) : !slowGather)) {
+            (kSplitAhead ? aligned(Ix, sX, -1) : vecX && vecY)) {
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw * cuShare);
@@ -724,7 +756,27 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             cd.kind = 4;
             cd.tMfma = tMfma / kSplitWait * c.eff / c.deff;
             cd.tMem = tMem;
-            cd.cost = bound(std::max(cd.tMfma, tMem), tChain);
+            cd.cost = bound(std::max(cd.tMfma, tMem), tChain) + tileSetup;
+            ranked.push_back(cd);
+        }
+        // The same kernel with element-wise copies, for operands that do not
+        // both gather in vectors (fp32): the boxes run over the linearised
+        // contracted set, so only the last one is padded, and offsets within
+        // an operand take 32 bits.
+        if (c.deff > 0.0f && dtype == GETT_FLOAT32 && !(vecX && vecY) && !kSplitAhead &&
+            !an.emptySum && an.sizeK < INT32_MAX / 2 && an.maxOffA < INT32_MAX &&
+            an.maxOffB < INT32_MAX) {
+            const double tMem = (bytesC + bytesX + bytesY +
+                                 0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
+                                (8.0e12 * c.bw * cuShare);
+            const double boxes = std::ceil((double)an.sizeK / c.kt);
+            Candidate cd;
+            cd.tile = t;
+            cd.kind = 6;
+            cd.tMfma = tMfma * boxes * c.kt / kpad / kElementWise * c.eff /
+                       (wpt >= 8 ? 0.66 : 0.71);
+            cd.tMem = tMem;
+            cd.cost = bound(std::max(cd.tMfma, tMem), chain(tx * ty, boxes)) + tileSetup;
             ranked.push_back(cd);
         }
         // Persistent direct-load kernel (tiles that carry it): a contracted
@@ -811,7 +863,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const int occ = (int)tail_occupancy(c, itemB);
             const double boxFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * c.kt * 2.0;
             const double boxTime =
-                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) * kSplitWait;
+                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) * kSplitWait * kElementWise;
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw);
@@ -837,6 +889,21 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 }
             }
             if (best.tile >= 0) ranked.push_back(best);
+        }
+    }
+    // K slices also sum in shorter chains: over 3721 positions 4e-7 of the
+    // result's norm against 1.1e-6 in one chain (fp32).  A long contracted set
+    // that is sliced by the other kernels stays so beside the direct-load
+    // kernels of element-wise and split operands, which take it in one.
+    if (an.sizeK > 2048) {
+        const Candidate *other = nullptr;
+        for (const Candidate &c : ranked)
+            if (c.kind <= 3 && (!other || c.cost < other->cost)) other = &c;
+        if (other && other->kind == 2) {
+            const double floor = other->cost * 1.01;
+            for (Candidate &c : ranked)
+                if (c.kind == 6 || (c.kind == 4 && !(vecX && vecY)))
+                    c.cost = std::max(c.cost, floor);
         }
     }
     // Ties (the same estimate to 0.01 us: mirror-image tiles on a square
@@ -1122,6 +1189,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     d.kbox = (int32_t)kbox;
     d.nblk = (int32_t)std::max<int64_t>(nblk, 1);
     d.nblkInv = recip(d.nblk);
+    d.linK = kind == 6 ? (int32_t)an.sizeK : 0;
     d.nsteps = nsteps;
     // With C stored in its memory order a tile takes whole runs of C only (240
     // of 256 columns for runs of 24): a run cut by a tile's edge is written in

@@ -91,6 +91,8 @@ struct KDesc {
     int32_t kbox;                  // elements in one box = prod(earlier extents) * tj
     int32_t nblk;                  // blocks along index kj = ceil(extent of kj / tj)
     Recip nblkInv;
+    int32_t linK;                  // contracted positions, walked linearly by the
+                                   // element-wise direct-load kernel (0: none)
     int64_t nsteps;                // boxes = nblk * prod(later extents); 0 = empty sum
     // ---- grid ----
     int32_t tilesX, tilesY;        // tiles along x and y

@@ -400,6 +400,220 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
     w.template unpack<1>(Ct, offCx, offCy, alpha, beta, d.cvec != 0);
 }
 
+// ---------------------------------------------------------------------------
+// The direct-load kernel for operands that cannot be gathered in 16-byte
+// vectors (odd extents or strides, bases off the 16-byte grid): every element
+// is copied into LDS by a load of its own (global_load_lds_dword: lane i of
+// one instruction fills bytes [4 i, 4 i + 4) after the wave's LDS base).  The
+// LDS images are those of the vector copies, so the fragment reads, the MFMAs
+// and the pipeline are the same; four times the load instructions, but nothing
+// staged in registers and no alignment to ask for.
+//
+// Since any element may go to any place, the boxes need not follow the
+// indices: box s is positions [s KT, (s + 1) KT) of the linearised contracted
+// set, whose offsets are decoded into a small LDS table two boxes ahead.  Only
+// the last box can be partial (an extent of 23 in a box of 32 idled 28% of
+// the MFMAs).
+//
+// Bound by the MFMAs on large contractions: 192 load instructions per box of
+// a 128 x 256 tile against 8192 cycles of MFMAs per SIMD.
+template <typename T, int ROWS, int KT, bool KF, int NTH, int R>
+struct ElementOperand {
+    static_assert(sizeof(T) == 4, "one dword per element");
+    static constexpr int VW = Traits<T>::VW;
+    static constexpr int NW = NTH / 64;
+    static constexpr int CPR = KT / VW;
+    static constexpr int J = ROWS * KT / NTH;   // elements per thread
+    // KF: lanes along k, [row][k] with the pieces of a row permuted as for
+    // the k-vector copy.  A thread's rows are NTH / KT apart, so its position
+    // in the row repeats every P elements.
+    static constexpr int P = KF ? (CPR * R * KT / NTH > 1 ? CPR * R * KT / NTH : 1) : 1;
+    static_assert(!KF || (NTH % KT == 0 && (NTH / KT) % R == 0 && J % P == 0), "rows per round");
+    // otherwise lanes along the rows, [k][row]: one row per thread, one
+    // position per wave and element
+    static_assert(KF || (NTH % ROWS == 0 && ROWS % 64 == 0 && KT <= 64), "one row per thread");
+
+    uint32_t row[KF ? J : 1];   // operand offset of the element's row
+    int kk[P];                  // its box position
+    int lane, wave;
+
+    // rowoff: LDS table of operand offsets per tile row; rows outside the
+    // tensor load the tile's first row, and nothing reads their results
+    __device__ __forceinline__ void setup(int tid, int w, const int *rowoff)
+    {
+        lane = tid & 63;
+        wave = w;
+        if constexpr (KF) {
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int p = (j * NW + w) * 64 + lane, r = p / KT, c = p % KT;
+                row[j] = (uint32_t)max(rowoff[r], 0);
+                if (j < P) kk[j] = VW * kvec_piece<CPR, R>(r, c / VW) + c % VW;
+            }
+        } else {
+            row[0] = (uint32_t)max(rowoff[tid % ROWS], 0);
+            kk[0] = 0;
+        }
+    }
+
+    // copy this thread's elements of the box whose positions have the offsets
+    // `koff` (LDS; -1 past the last position, looked for when CHECK) into `dst`
+    template <bool CHECK>
+    __device__ __forceinline__ void issue(const T *base, T *dst, const int *koff) const
+    {
+        int ko[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) ko[i] = koff[KF ? kk[i] : lane & (KT - 1)];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            T *slot = dst + (j * NW + wave) * 64;
+            int k;
+            if constexpr (KF) k = ko[j % P];
+            else k = __builtin_amdgcn_readlane(ko[0], (j * NW + wave) * 64 / ROWS);
+            if (CHECK && k < 0)
+                slot[lane] = T(0);
+            else
+                __builtin_amdgcn_global_load_lds(
+                    (global_void *)(base + (row[KF ? j : 0] + (uint32_t)k)), (lds_void *)slot, 4, 0,
+                    0);
+        }
+    }
+};
+
+template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY, bool XKF, bool YKF>
+__global__ void __launch_bounds__(WM *WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
+gett_element_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ Y,
+                    T *__restrict__ C, const T alpha, const T beta)
+{
+    constexpr int NTH = WM * WN * 64;
+    constexpr int VW = Traits<T>::VW;
+    constexpr int NG = KT / (4 * VW);   // step groups per box
+    typedef WaveTile<T, MT, NT, KT, WM, WN, RX, RY> WT;
+    typedef ElementOperand<T, MT, KT, XKF, NTH, RX> OX;
+    typedef ElementOperand<T, NT, KT, YKF, NTH, RY> OY;
+    typedef DirectFrag<T, XKF ? kGatherKVec : kGatherRowVec, WT::RB, RX, MT, KT> FX;
+    typedef DirectFrag<T, YKF ? kGatherKVec : kGatherRowVec, WT::CB, RY, NT, KT> FY;
+    constexpr int STAGE = (MT + NT) * KT;
+
+    extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
+    T *panels = reinterpret_cast<T *>(dyn_lds);
+    __shared__ int rowX[MT], rowY[NT], offCx[MT], offCy[NT];
+    constexpr int kAhead = 4;   // boxes whose positions are decoded at a time
+    __shared__ int kX[2 * kAhead][KT], kY[2 * kAhead][KT];
+    static_assert(kAhead * KT <= NTH, "one position per thread");
+
+    const int tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    touch_arguments();
+    const int ntiles = d.tilesX * d.tilesY;
+    const int nbox = (d.linK + KT - 1) / KT;
+    // offsets of position t of box s into its table set
+    auto positions = [&](int s, int t) {
+        uint32_t k = (uint32_t)(s * KT + t);
+        const bool in = k < (uint32_t)d.linK;
+        uint32_t ox = 0, oy = 0;
+        for (int i = 0; i < d.nk; ++i) {
+            const KDim &ki = d.k()[i];
+            const uint32_t id = digit(k, ki);
+            ox += id * (uint32_t)ki.s0;
+            oy += id * (uint32_t)ki.s1;
+        }
+        kX[s % (2 * kAhead)][t] = in ? (int)ox : -1;
+        kY[s % (2 * kAhead)][t] = in ? (int)oy : -1;
+    };
+    if (tid < 2 * KT) positions(tid / KT, tid % KT);
+    WT w;
+    w.init(tid);
+    int tx, ty;
+    tile_of_block(d, d.tile0 + (int)blockIdx.x, ntiles, tx, ty);
+    const TileBase tb = tile_base<MT, NT>(d, tx, ty);
+    tile_tables<MT, NT, NTH>(d, tx, ty, tb, tid, rowX, offCx, rowY, offCy);
+    const T *Xt = X + tb.x;
+    const T *Yt = Y + tb.y;
+    __syncthreads();
+
+    OX ox;
+    OY oy;
+    ox.setup(tid, wave, rowX);
+    oy.setup(tid, wave, rowY);
+    w.zero();
+    const int l16 = tid & 15, g = (tid & 63) >> 4;
+    const int xw = w.wm * WT::WTM, yw = w.wn * WT::WTN;
+    const int whole = d.linK / KT;   // boxes before this one have KT positions
+    auto issue = [&](int s) {
+        T *st = panels + (s & 1) * STAGE;
+        if (s < whole) {
+            ox.template issue<false>(Xt, st, kX[s % (2 * kAhead)]);
+            oy.template issue<false>(Yt, st + MT * KT, kY[s % (2 * kAhead)]);
+        } else {
+            ox.template issue<true>(Xt, st, kX[s % (2 * kAhead)]);
+            oy.template issue<true>(Yt, st + MT * KT, kY[s % (2 * kAhead)]);
+        }
+    };
+    auto read = [&](FX (&fx)[NG], FY (&fy)[NG], int buf) {
+        const T *st = panels + buf * STAGE;
+#pragma unroll
+        for (int grp = 0; grp < NG; ++grp) {
+            fx[grp].read(st, xw, l16, g, grp);
+            fy[grp].read(st + MT * KT, yw, l16, g, grp);
+        }
+    };
+    auto mma = [&](const FX &fx, const FY &fy) {
+#pragma unroll
+        for (int s4 = 0; s4 < VW; ++s4)
+#pragma unroll
+            for (int a = 0; a < WT::RB; ++a)
+#pragma unroll
+                for (int b = 0; b < WT::CB; ++b)
+                    w.acc[a][b] = mfma16x16x4(fx.at(a, s4), fy.at(b, s4), w.acc[a][b]);
+    };
+    auto barrier = []() { asm volatile("s_barrier" ::: "memory"); };
+    constexpr int kVmLgk0 = 7 << 4;   // vmcnt 0, lgkmcnt 0
+
+    // The pipeline of gett_direct_kernel.  Every kAhead boxes, before the
+    // barrier that the loads of box s + 2 follow, the positions of boxes
+    // s + 2 .. s + kAhead + 1 are decoded; the sets they replace were read
+    // for boxes up to s + 1 - kAhead, issued at least kAhead barriers ago.
+    // (Decoding one box at a time cost 5% of the 4096^3 contraction.)
+    if (nbox > 0) {
+        FX fx[NG];
+        FY fy[NG];
+        issue(0);
+        if (nbox > 1) issue(1);
+        __builtin_amdgcn_s_waitcnt(kVmLgk0);
+        barrier();
+        read(fx, fy, 0);
+        for (int s = 0; s + 1 < nbox; ++s) {
+            if (s % kAhead == 0 && tid < kAhead * KT) positions(s + 2 + tid / KT, tid % KT);
+#pragma unroll
+            for (int grp = 0; grp + 1 < NG; ++grp) mma(fx[grp], fy[grp]);
+            __builtin_amdgcn_s_waitcnt(kVmLgk0);   // box s + 1 loaded, box s read
+            barrier();
+            if (s + 2 < nbox) issue(s + 2);
+            FX gx[NG];
+            FY gy[NG];
+            read(gx, gy, (s + 1) & 1);
+            mma(fx[NG - 1], fy[NG - 1]);
+            constexpr int NREAD = NG * (FX::kReads + FY::kReads);
+            constexpr int NMFMA = VW * WT::RB * WT::CB;
+#pragma unroll
+            for (int r = 0; r < NREAD; ++r) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, NMFMA / NREAD > 0 ? NMFMA / NREAD : 1,
+                                                     0);
+            }
+#pragma unroll
+            for (int grp = 0; grp < NG; ++grp) {
+                fx[grp] = gx[grp];
+                fy[grp] = gy[grp];
+            }
+        }
+#pragma unroll
+        for (int grp = 0; grp < NG; ++grp) mma(fx[grp], fy[grp]);
+    }
+    w.template unpack<1>(C + (tb.cx + tb.cy), offCx, offCy, alpha, beta, d.cvec != 0);
+}
+
 // Persistent direct-load kernel for plans whose contracted set is one K box.
 // Workgroups walk tiles t = tile0 + blockIdx.x, + gridDim.x, ...; tile t's box
 // sits in LDS buffer t mod 2 (per workgroup).  Per tile:

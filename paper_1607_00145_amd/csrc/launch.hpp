@@ -124,6 +124,27 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
             k, dim3(tiles - (unsigned)d.tile0), dim3(threads), lds, stream, d,
             static_cast<const T *>(X), static_cast<const T *>(Y), static_cast<T *>(C),
             static_cast<T>(alpha), static_cast<T>(beta));
+    } else if constexpr (KIND == 6) {
+        if (d.kslices > 1) return hipErrorInvalidValue;   // whole tiles only
+        if ((unsigned)d.tile0 >= tiles) return hipSuccess;
+        // lanes along each operand's contracted or free index, whichever has
+        // the smaller stride
+        constexpr size_t lds = 2 * (size_t)(t.mt + t.nt) * t.kt * sizeof(T);
+        hipError_t e = hipSuccess;
+        auto go = [&](auto xkf, auto ykf) {
+            constexpr auto k = gett_element_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry,
+                                                   decltype(xkf)::value, decltype(ykf)::value>;
+            e = allow_dynamic_lds<k>(lds);
+            if (e != hipSuccess) return;
+            hipLaunchKernelGGL(k, dim3(tiles - (unsigned)d.tile0), dim3(threads), lds, stream, d,
+                               static_cast<const T *>(X), static_cast<const T *>(Y),
+                               static_cast<T *>(C), static_cast<T>(alpha), static_cast<T>(beta));
+        };
+        typedef std::true_type Yes;
+        typedef std::false_type No;
+        if (d.xscalar_kfast) d.yscalar_kfast ? go(Yes(), Yes()) : go(Yes(), No());
+        else d.yscalar_kfast ? go(No(), Yes()) : go(No(), No());
+        if (e != hipSuccess) return e;
     } else if constexpr (KIND == 5) {
         if (d.kslices > 1 || d.nsteps != 1) return hipErrorInvalidValue;   // one K box
         if ((unsigned)d.tile0 >= tiles) return hipSuccess;
@@ -163,6 +184,8 @@ LaunchFn pick_modes(int xm, int ym, int kind)
     constexpr bool kTail = TileTable<T>::tiles[TI].tail != 0;
     constexpr bool kDirect = TileTable<T>::tiles[TI].deff > 0.0f;
     constexpr bool kDStream = TileTable<T>::tiles[TI].dsbw > 0.0f;
+    constexpr bool kElement = kDirect && sizeof(T) == 4;
+    if (kind == 6 && kElement) return &launch_one<T, TI, 0, 0, kElement ? 6 : 0>;   // any modes
 #define GETT_CASE(a, b)                                                                       \
     if (xm == a && ym == b) {                                                                 \
         constexpr bool kDir = kDirect && direct_modes(a, b);                                  \
