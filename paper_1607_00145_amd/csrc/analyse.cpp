@@ -814,7 +814,23 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             b.nsteps >= 16) {
             Candidate best;
             best.tile = -1;
-            for (int P = 2; P <= 256 && b.nsteps / P >= 8; P *= 2) {
+            // Tiles that carry the direct-load kernel slice on it (both operands
+            // in vectors): its MFMA rate, the slots summed by a second launch
+            // (6 us), as many slices as fill the workgroups the CUs hold at
+            // once (two of 128 x 128, one of eight wavefronts), and a
+            // workspace within the 64 MB of gett_contract_noalloc.
+            const bool directSlices =
+                c.deff > 0.0f && vecX && vecY && !kSplitAhead && !(flags & GETT_FLAG_SCALAR);
+            std::vector<int> counts;
+            for (int P = 2; P <= 256; P *= 2) counts.push_back(P);
+            if (directSlices) {
+                counts.clear();
+                const double resident = wpt >= 8 ? 256.0 : 512.0;
+                if (resident / (tx * ty) >= 2.0) counts.push_back((int)(resident / (tx * ty)));
+            }
+            for (int P : counts) {
+                if (b.nsteps / P < 8) continue;
+                if (directSlices && tx * ty * P * tileBytes > 64.0e6) continue;
                 const double wgs = tx * ty * P;
                 const double perSimdP =
                     wpt >= 4 ? cu_time((int)tail_occupancy(c, itemB), (int)std::ceil(wgs / 256.0),
@@ -823,14 +839,15 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                              : std::ceil(wgs * wpt / 1024.0);
                 const double kpadP = (std::ceil((double)b.nsteps / P) + 2.0) * c.kt;
                 const double tM = perSimdP * (double)(c.mt / c.wm) * (c.nt / c.wn) * kpadP * 2.0 /
-                                  (peakSimd * c.eff) *
+                                  (peakSimd * (directSlices ? c.deff : c.eff)) *
                                   (kSplitAhead && c.nbuf == 1 ? 1.4 : 1.0);
                 const double shareP = std::min(1.0, wgs / 256.0);
                 const double tMemP = (bytesC + bytesX + bytesY +
                                       0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                      (8.0e12 * c.bw * shareP);
                 const double tPart =
-                    tx * ty * tileBytes * 2.0 * P / kPartialBw + P * tileBytes / kSumBw + 1.0e-6;
+                    tx * ty * tileBytes * 2.0 * P / kPartialBw +
+                    (directSlices ? 6.0e-6 : P * tileBytes / kSumBw + 1.0e-6);
                 const double tChainP = chain(wgs, std::ceil((double)b.nsteps / P));
                 const double cost = bound(std::max(tM, tMemP), tChainP) + tPart;
                 if (best.tile < 0 || cost < best.cost) {
@@ -895,7 +912,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     // result's norm against 1.1e-6 in one chain (fp32).  A long contracted set
     // that is sliced by the other kernels stays so beside the direct-load
     // kernels of element-wise and split operands, which take it in one.
-    if (an.sizeK > 2048) {
+    if (an.sizeK > 3000) {
         const Candidate *other = nullptr;
         for (const Candidate &c : ranked)
             if (c.kind <= 3 && (!other || c.cost < other->cost)) other = &c;

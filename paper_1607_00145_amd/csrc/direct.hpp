@@ -221,7 +221,7 @@ struct DirectWalk {
     uint32_t next;
     int blk, c1, nblk, e1, ek, tj;
 
-    __device__ __forceinline__ void init(const KDesc &d)
+    __device__ __forceinline__ void init(const KDesc &d, uint32_t s0)
     {
         const KDim &kj = d.k()[d.kj];
         nblk = d.nblk > 0 ? d.nblk : 1;
@@ -233,10 +233,11 @@ struct DirectWalk {
         e1 = later ? d.k()[d.kj + 1].ext : 0;
         sx1 = later ? d.k()[d.kj + 1].s0 : 0;
         sy1 = later ? d.k()[d.kj + 1].s1 : 0;
-        next = 0;
-        blk = 0;
-        c1 = 0;
-        box_origin(d, 0, ox, oy);
+        next = s0;
+        uint32_t rest = quotient(s0, nblk, d.nblkInv);
+        blk = (int)(s0 - rest * (uint32_t)nblk);
+        c1 = later ? (int)digit(rest, d.k()[d.kj + 1]) : 0;
+        box_origin(d, s0, ox, oy);
     }
     // origin of box `next` and its valid positions along index kj; then step
     // to the box after it
@@ -266,11 +267,14 @@ struct DirectWalk {
     }
 };
 
+// One workgroup of the direct-load kernel: boxes [s0, s0 + nsteps) of tile
+// `tile`, stored with alpha / beta, or (SLICED) left as a partial tile in `W`.
 template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY, int XMODE,
-          int YMODE, bool WHOLE>
-__global__ void __launch_bounds__(WM *WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
-gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ Y,
-                   T *__restrict__ C, const T alpha, const T beta)
+          int YMODE, bool WHOLE, bool SLICED>
+__device__ __forceinline__ void direct_tile(const KDesc &d, const T *__restrict__ X,
+                                            const T *__restrict__ Y, T *__restrict__ C,
+                                            const T alpha, const T beta, int tile, uint32_t s0,
+                                            uint32_t nsteps, T *__restrict__ W)
 {
     constexpr int NTH = WM * WN * 64;
     constexpr int VW = Traits<T>::VW;
@@ -299,7 +303,7 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
     WT w;
     w.init(tid);
     int tx, ty;
-    tile_of_block(d, d.tile0 + (int)blockIdx.x, ntiles, tx, ty);
+    tile_of_block(d, tile, ntiles, tx, ty);
     const TileBase tb = tile_base<MT, NT>(d, tx, ty);
     tile_tables<MT, NT, NTH>(d, tx, ty, tb, tid, rowX, offCx, rowY, offCy);
     const T *Xt = X + tb.x;
@@ -313,13 +317,12 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
     ox.setup(tid, rowX, kX, kco);
     oy.setup(tid, rowY, kY, kco, es);
     w.zero();
-    const uint32_t nsteps = (uint32_t)d.nsteps;
     const int l16 = tid & 15, g = (tid & 63) >> 4;
     const int xw = w.wm * WT::WTM, yw = w.wn * WT::WTN;
 
     DirectWalk walk;
-    if (nsteps > 0) walk.init(d);
-    auto issue = [&](int buf) {   // the boxes in order: 0, 1, 2, ...
+    if (nsteps > 0) walk.init(d, s0);
+    auto issue = [&](int buf) {   // the boxes in order: s0, s0 + 1, ...
         int64_t bx, by;
         const int lim = walk.take(d, bx, by);
         T *st = panels + buf * STAGE;
@@ -397,7 +400,107 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
 #pragma unroll
         for (int grp = 0; grp < NG; ++grp) mma(fx[grp], fy[grp]);
     }
-    w.template unpack<1>(Ct, offCx, offCy, alpha, beta, d.cvec != 0);
+    if constexpr (SLICED) {
+#pragma unroll
+        for (int a = 0; a < WT::RB; ++a)
+#pragma unroll
+            for (int b = 0; b < WT::CB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    W[(size_t)(((a * WT::CB + b) * 4 + r) * NTH + tid)] = w.acc[a][b][r];
+    } else {
+        w.template unpack<1>(Ct, offCx, offCy, alpha, beta, d.cvec != 0);
+    }
+}
+
+template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY, int XMODE,
+          int YMODE, bool WHOLE>
+__global__ void __launch_bounds__(WM *WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
+gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ Y,
+                   T *__restrict__ C, const T alpha, const T beta)
+{
+    direct_tile<T, MT, NT, KT, WM, WN, RX, RY, XMODE, YMODE, WHOLE, false>(
+        d, X, Y, C, alpha, beta, d.tile0 + (int)blockIdx.x, 0, (uint32_t)d.nsteps, nullptr);
+}
+
+// K slices on the direct-load kernel: workgroup b computes slice b / tiles of
+// tile b % tiles into slot b of the workspace (the slots of the macro-kernel's
+// K slices), and gett_sum_slices_kernel adds a tile's slots in slice order.
+// Bound by the MFMAs: a C of 384 x 376 over 144384 is 9 tiles of 128 x 128,
+// 56 slices of which fill the CUs twice, against 72 tiles of 32 x 64 (64
+// slices), the largest for which the last workgroup of a tile can sum its
+// slots in turn without dominating.  432 us on those, 351 us here.
+// Consecutive workgroups of one XCD share a slice's panels in its L2.
+template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY, int XMODE,
+          int YMODE, bool WHOLE>
+__global__ void __launch_bounds__(WM *WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
+gett_direct_slice_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ Y,
+                         T *__restrict__ W)
+{
+    const int ntiles = d.tilesX * d.tilesY, n = ntiles * d.kslices, full = n & ~7;
+    const int bid = (int)blockIdx.x;
+    const int b = bid < full ? (bid & 7) * (full >> 3) + (bid >> 3) : bid;
+    const int slice = b / ntiles, u = b - slice * ntiles;
+    // nsteps < 2^31 and kslices < 2^31 / threads: the products need 64 bits
+    const uint32_t s0 = (uint32_t)((uint64_t)d.nsteps * (uint32_t)slice / (uint32_t)d.kslices);
+    const uint32_t s1 = (uint32_t)((uint64_t)d.nsteps * (uint32_t)(slice + 1) / (uint32_t)d.kslices);
+    direct_tile<T, MT, NT, KT, WM, WN, RX, RY, XMODE, YMODE, WHOLE, true>(
+        d, X, Y, nullptr, T(0), T(0), u, s0, s1 - s0, W + (size_t)b * (MT * NT));
+}
+
+// C <- alpha * (the sum of a tile's slots, in slice order) + beta * C.  One
+// workgroup per MFMA block position (a, b) of the register tile, so that a
+// tile's slots are read by 16 workgroups at once; eight slots in flight per
+// thread.  Bound by the slots' stream from L2 and the Infinity Cache.
+template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY>
+__global__ void __launch_bounds__(WM *WN * 64)
+gett_sum_slices_kernel(const KDesc d, const T *__restrict__ W, T *__restrict__ C, const T alpha,
+                       const T beta)
+{
+    constexpr int NTH = WM * WN * 64;
+    constexpr int kFlight = 8;
+    typedef WaveTile<T, MT, NT, KT, WM, WN, RX, RY> WT;
+    const int ntiles = d.tilesX * d.tilesY;
+    const int u = (int)blockIdx.x / (WT::RB * WT::CB);
+    const int blk = (int)blockIdx.x - u * (WT::RB * WT::CB);   // a * CB + b
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const T *slot = W + (size_t)u * (MT * NT) + (size_t)blk * 4 * NTH + tid;
+    const size_t step = (size_t)ntiles * (MT * NT);
+    T sum[4];
+    for (int p0 = 0; p0 < d.kslices; p0 += kFlight) {
+        T v[kFlight][4];
+#pragma unroll
+        for (int q = 0; q < kFlight; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                v[q][r] = p0 + q < d.kslices ? slot[(size_t)(p0 + q) * step + r * NTH] : T(0);
+#pragma unroll
+        for (int q = 0; q < kFlight; ++q)
+            if (p0 + q < d.kslices) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum[r] = p0 + q == 0 ? v[q][r] : sum[r] + v[q][r];
+            }
+    }
+    int tx, ty;
+    tile_of_block(d, u, ntiles, tx, ty);
+    auto offset = [](uint32_t v, int n, const KDim *set) {
+        int64_t o = 0;
+        for (int i = 0; i < n; ++i) o += (int64_t)digit(v, set[i]) * set[i].s1;
+        return o;
+    };
+    const int col = (wave / WM) * WT::WTN + block_row<RY>(blk % WT::CB, lane & 15);
+    const uint32_t y = (uint32_t)(ty * NT + col);
+    if ((int64_t)y >= d.sizeY) return;
+    const int64_t oy = offset(y, d.ny, d.y());
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = (wave % WM) * WT::WTM +
+                        block_row<RX>(blk / WT::CB, Traits<T>::mrow(lane >> 4, r));
+        const uint32_t x = (uint32_t)(tx * MT + row);
+        if ((int64_t)x >= d.sizeX) continue;
+        T *c = C + (oy + offset(x, d.nx, d.x()));
+        *c = beta != T(0) ? alpha * sum[r] + beta * *c : alpha * sum[r];
+    }
 }
 
 // ---------------------------------------------------------------------------

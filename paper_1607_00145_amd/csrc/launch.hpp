@@ -85,6 +85,28 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
             static_cast<T>(alpha), static_cast<T>(beta), static_cast<T *>(nullptr), nullptr);
     } else if constexpr (KIND == 2) {
         if (d.kslices < 2 || d.tile0 != 0) return hipErrorInvalidValue;
+        if constexpr (t.deff > 0.0f && direct_modes(XM, YM)) {
+            // tiles that carry the direct-load kernel slice on it
+            const bool whole = d.kbox == t.kt && d.k()[d.kj].ext % d.tj == 0;
+            constexpr auto kWhole = gett_direct_slice_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx,
+                                                             t.ry, XM, YM, true>;
+            constexpr auto kPart = gett_direct_slice_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx,
+                                                            t.ry, XM, YM, false>;
+            constexpr size_t lds = 2 * (size_t)(t.mt + t.nt) * t.kt * sizeof(T);
+            const hipError_t e =
+                whole ? allow_dynamic_lds<kWhole>(lds) : allow_dynamic_lds<kPart>(lds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(whole ? kWhole : kPart, dim3(tiles * (unsigned)d.kslices),
+                               dim3(threads), lds, stream, d, static_cast<const T *>(X),
+                               static_cast<const T *>(Y), static_cast<T *>(w.tiles));
+            constexpr unsigned blocks = (t.mt / t.wm / 16) * (t.nt / t.wn / 16);
+            hipLaunchKernelGGL(
+                (gett_sum_slices_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry>),
+                dim3(tiles * blocks), dim3(threads), 0, stream, d,
+                static_cast<const T *>(w.tiles), static_cast<T *>(C), static_cast<T>(alpha),
+                static_cast<T>(beta));
+            return hipGetLastError();
+        }
         hipLaunchKernelGGL(
             (gett_macro_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, t.wpe, t.pf, t.nbuf, XM,
                                YM, t.onebox, t.corder, 0, 1>),
