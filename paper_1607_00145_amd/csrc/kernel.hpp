@@ -801,6 +801,59 @@ struct WaveTile {
                                                         reinterpret_cast<vec *>(C + ox[q] + oy[cg]));
                         }
                 }
+            } else if constexpr (kVecC) {
+                // C off the 16-byte grid (odd extents, strides or base): a
+                // lane's VW columns are still one vector where they follow
+                // one another in C -- device memory takes 16-byte accesses at
+                // any element address -- and single elements only where a
+                // group is cut by the end of a run or of C.
+                typedef vec uvec __attribute__((aligned(sizeof(T))));
+                int oy[CB];
+                bool run[CGV];
+#pragma unroll
+                for (int cg = 0; cg < CGV; ++cg) {
+#pragma unroll
+                    for (int j = 0; j < VW; ++j) oy[cg * VW + j] = offCy[col_of(cg) + j];
+                    run[cg] = oy[cg * VW] >= 0;
+#pragma unroll
+                    for (int j = 1; j < VW; ++j)
+                        run[cg] = run[cg] && oy[cg * VW + j] == oy[cg * VW] + j;
+                }
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    if (!ALL && ox[q] < 0) continue;
+                    uvec cv[CGV];
+                    if (readC) {
+#pragma unroll
+                        for (int cg = 0; cg < CGV; ++cg) {
+                            if (run[cg]) {
+                                cv[cg] = *reinterpret_cast<const uvec *>(C + ox[q] + oy[cg * VW]);
+                            } else {
+#pragma unroll
+                                for (int j = 0; j < VW; ++j)
+                                    if (ALL || oy[cg * VW + j] >= 0)
+                                        cv[cg][j] = C[ox[q] + oy[cg * VW + j]];
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int cg = 0; cg < CGV; ++cg) {
+                        uvec out;
+#pragma unroll
+                        for (int j = 0; j < VW; ++j) {
+                            const T a = alpha * acc[grp * RX + q / 4][cg * RY + j][q % 4];
+                            out[j] = readC ? a + beta * cv[cg][j] : a;
+                        }
+                        if (run[cg]) {
+                            *reinterpret_cast<uvec *>(C + ox[q] + oy[cg * VW]) = out;
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < VW; ++j)
+                                if (ALL || oy[cg * VW + j] >= 0)
+                                    C[ox[q] + oy[cg * VW + j]] = out[j];
+                        }
+                    }
+                }
             } else {
                 int oy[CB];
 #pragma unroll
