@@ -620,6 +620,12 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         return !(flags & GETT_FLAG_SCALAR) && (row || (kvec_ok(strOf) && aligned(I, strOf, -1)));
     };
     const bool vecX = vectors(Ix, sX), vecY = vectors(Iy, sY);
+    // Y's stride-one index among its free ones, behind C's: gathered in
+    // strided vectors where the column split below applies.
+    const int yUnit = unit_in(Iy, sY);
+    const bool vecYSplit = maySplit && yUnit > 0 && Iy[0].strC == 1 &&
+                           Iy[yUnit].extent % VW == 0 && pow2_part(Iy[0].extent) >= VW &&
+                           aligned(Iy, sY, yUnit) && aligned(Ik, sY, -1);
     const bool vecC = Iy[0].strC == 1 && Iy[0].extent % VW == 0;
     // Partial tiles (K slices, stream-K tail) are summed through the
     // workspace: the stream of partial tiles and one workgroup's reads of a
@@ -640,7 +646,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // operands are both gathered in vectors: it waits for each operand's
         // gathers in turn, which element-wise gathers make long (it still
         // runs any plan it is forced onto)
-        if (c.onebox && (box_for(c.kt).nsteps > 1 || slowGather) && !(ft && atoi(ft) == t) &&
+        if (c.onebox && (box_for(c.kt).nsteps > 1 || slowGather || !(vecX && vecY)) && !(ft && atoi(ft) == t) &&
             !(force && force->tile == t))
             continue;
         std::vector<Index> ksplit;
@@ -681,12 +687,22 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // wavefronts per SIMD this much of their MFMA rate (odd extents
         // against even ones: 4096^3-shaped 1.1-1.25, C of 529 x 3721 over 3721
         // 1.45 on 32 x 64 tiles).
-        const double kElementWise = dtype != GETT_FLOAT32 || (vecX && vecY) || kSplitAhead ? 1.0
-                                    : c.mt * c.nt <= 32 * 64                               ? 1.3
-                                    : c.wpe == 1                                           ? 1.2
-                                                                                           : 1.1;
+        const bool elements =
+            slowGather || !(vecX && (vecY || vecYSplit || kSplitAhead));   // some operand's
+        const double kElementWise = dtype != GETT_FLOAT32 || (vecX && (vecY || vecYSplit)) ||
+                                            kSplitAhead
+                                        ? 1.0
+                                    : c.mt * c.nt <= 32 * 64 ? 1.3
+                                    : c.wpe == 1             ? 1.2
+                                                             : 1.1;
+        // Operands stride-one along different contracted indices that refuse
+        // the split: one of them takes another cache line per element, the
+        // more boxes, the more often (fp32, 53 x 51 x 50 x 49 over 47 x 45:
+        // 128 x 128 x 16 tiles 810 us, 256 x 128 x 32 element-wise 554).
+        const bool crossed = !kSplitAhead && splitXK >= 0 && splitYK >= 0 && splitXK != splitYK;
+        const double kCrossed = crossed && dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.0 : 1.0;
         const double tMfma =
-            perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait * kElementWise;
+            perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait * kElementWise * kCrossed;
         // A tile's offset tables, first gathers and C stores are covered by
         // nothing when its workgroup has the CU to itself (measured per tile
         // on fp32 tensors times matrices with contracted sets of 96-384: 4 us
@@ -726,9 +742,15 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const double bwFrac = (k ? c.sbw : c.bw) * cuShare;
             // compulsory bytes (each operand read once, C written once) plus
             // the operand panels re-read by other tiles, mostly from L2
+            // A single LDS buffer does not overlap the boxes of an fp64 stream
+            // (C of 24 x 373248 over 72: 82 us on 64 x 128, 60 on 32 x 64).
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
-                                (8.0e12 * bwFrac);
+                                (8.0e12 * bwFrac) *
+                                (dtype != GETT_FLOAT64                  ? 1.0
+                                 : c.nbuf == 1 && b.nsteps > 1          ? 1.4
+                                 : elements && c.mt * c.nt <= 32 * 64 ? 1.25
+                                                                      : 1.0);
             Candidate cd;
             cd.tile = t;
             cd.kind = k;
@@ -736,7 +758,16 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             cd.tMem = tMem;
             // element-wise gathers into a single LDS buffer (the streaming
             // kernel too) wait with nothing to overlap them, as in the K split
-            const double single = (slowGather && (c.nbuf == 1 || k == 1)) ? 1.4 : 1.0;
+            // (the fp32 tiles 256 wide carry sixteen such loads per thread and
+            // box: 2.2, 1.7 with more workgroups per CU on 32 rows; one
+            // wavefront alone on 64 x 64 1.5)
+            const double single =
+                !elements                                             ? 1.0
+                : c.nbuf == 1 || k == 1                               ? 1.4
+                : slowGather && vecX && vecYSplit                     ? 1.0
+                : dtype == GETT_FLOAT32 && c.nt == 256 && c.kt == 16  ? (c.mt == 32 ? 1.7 : 2.2)
+                : dtype == GETT_FLOAT32 && wpt == 1                   ? 1.5
+                                                                      : 1.0;
             cd.cost = bound(std::max(tMfma, tMem), tChain) * single + macroSetup;
             ranked.push_back(cd);
         }
@@ -774,7 +805,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             cd.tile = t;
             cd.kind = 6;
             cd.tMfma = tMfma * boxes * c.kt / kpad / kElementWise * c.eff /
-                       (wpt >= 8 ? 0.66 : 0.71);
+                       (wpt >= 8 ? 0.71 : 0.68) * (crossed && c.mt < 256 ? 1.4 : 1.0);
             cd.tMem = tMem;
             cd.cost = bound(std::max(cd.tMfma, tMem), chain(tx * ty, boxes)) + tileSetup;
             ranked.push_back(cd);
@@ -786,8 +817,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // slower than the macro-kernel on the fp64 6D contractions of
         // Appendix A whose y set leads with one index of 24, 3-5% faster
         // on those whose y set leads with a merged run of 384).
-        if (c.dsbw > 0.0f && !slowGather && !(flags & GETT_FLAG_SCALAR) && !kSplitAhead &&
-            b.nsteps == 1) {
+        if (c.dsbw > 0.0f && vecX && vecY && !kSplitAhead && b.nsteps == 1) {
             const double dbw = cRunY >= c.nt ? c.dsbw : c.bw;
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
@@ -859,6 +889,16 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                     best.cost = cost;
                 }
             }
+            // (element-wise gathers wait in turn into one LDS buffer; in fp32
+            // measured 1.1-1.2 times the model's time, on 128 x 128 x 32
+            // 1.2-1.6)
+            if (elements && !kSplitAhead)
+                best.cost *= c.nbuf == 1                              ? 1.5
+                             : dtype != GETT_FLOAT32                  ? 1.0
+                             : c.nt == 256 && c.kt == 16 && c.mt < 64 ? 1.7
+                             : crossed                                ? 1.0
+                             : c.wpe == 1 && c.kt == 32               ? 1.35
+                                                                      : 1.15;
             if (best.tile >= 0) ranked.push_back(best);
         }
         // Stream-K tail: when the tiles do not fill the CUs a whole number of
@@ -880,7 +920,10 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const int occ = (int)tail_occupancy(c, itemB);
             const double boxFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * c.kt * 2.0;
             const double boxTime =
-                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) * kSplitWait * kElementWise;
+                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) * kSplitWait * kElementWise *
+                kCrossed * (elements && c.nbuf == 1 ? 2.5 : 1.0);   // spills (element-wise gathers in the
+                                                         // piece loop: 869 against 339 us on a C
+                                                         // of 529 x 3721 over 3721)
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw);
@@ -1067,6 +1110,15 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             }
         }
     }
+    // Y is stride-one along a free index behind C's, but extents or strides
+    // refuse the split: taken element by element in C's order, every lane
+    // reads another cache line and the rest of it is gone before the tile
+    // that needs it.  The index moves up behind C's, where the lanes can walk
+    // it (the lane order below) and neighbouring tiles find the lines in L2
+    // -- unless Y is so small beside C that it stays there anyway.
+    // (47 x 35 x 23 x 33 x 45 fp32 over 34: 1499 us, then 261 to 474 by tile.)
+    if (maySplit && !ysplit && !vecY && yUnit > 1 && Iy[0].strC == 1 && 4.0 * bytesY >= bytesC)
+        std::rotate(Iy.begin() + 1, Iy.begin() + yUnit, Iy.begin() + yUnit + 1);
     const Box box = box_for(ts.kt);
     // A contraction bound by the C stream walks C in memory order: x indices
     // by C stride (the row operand's stride-one index stays first when it is

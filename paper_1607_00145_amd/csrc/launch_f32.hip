@@ -22,10 +22,11 @@ template <> LaunchFn pick_tile<float, 5>(int, int, int);
 template <> LaunchFn pick_tile<float, 6>(int, int, int);
 template <> LaunchFn pick_tile<float, 7>(int, int, int);
 template <> LaunchFn pick_tile<float, 8>(int, int, int);
+template <> LaunchFn pick_tile<float, 9>(int, int, int);
 
 LaunchFn launch_fn_f32(int tile, int xm, int ym, int kind)
 {
-    static_assert(kNumTilesF32 == 9, "update the tile switch");
+    static_assert(kNumTilesF32 == 10, "update the tile switch");
     switch (tile) {
     case 0: return pick_tile<float, 0>(xm, ym, kind);
     case 1: return pick_tile<float, 1>(xm, ym, kind);
@@ -36,6 +37,7 @@ LaunchFn launch_fn_f32(int tile, int xm, int ym, int kind)
     case 6: return pick_tile<float, 6>(xm, ym, kind);
     case 7: return pick_tile<float, 7>(xm, ym, kind);
     case 8: return pick_tile<float, 8>(xm, ym, kind);
+    case 9: return pick_tile<float, 9>(xm, ym, kind);
     }
     return nullptr;
 }
