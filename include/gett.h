@@ -131,11 +131,13 @@ typedef struct gett_plan_s *gett_plan_t;
  * under the same values) and gett_plan_describe lists them ("hooks"):
  *   GETT_FORCE_TILE      tile index to use (gett_plan_describe "tile.id")
  *   GETT_FORCE_KIND      1 streaming kernel, 3 stream-K tail, 4 direct-load
- *                        kernel, 5 persistent direct-load kernel (on a tile
- *                        that carries it; the direct-load kernels also need
- *                        vector gathers of both operands, and the persistent
- *                        one a contracted set in one K box, else the plan
- *                        runs the tile's macro-kernel)
+ *                        kernel, 5 persistent direct-load kernel, 6 direct-
+ *                        load kernel with element-wise copies (on a tile
+ *                        that carries it; kinds 4 and 5 also need vector
+ *                        gathers of both operands, the persistent one a
+ *                        contracted set in one K box, else the plan runs the
+ *                        tile's macro-kernel; kind 6 takes the operands that
+ *                        do not gather in vectors)
  *   GETT_FORCE_KSLICES   number of K slices
  *   GETT_TAIL_WGS        workgroups of the stream-K tail
  *   GETT_SPLIT_F         block size of a split index (Sec. 3.2.1)
@@ -259,7 +261,7 @@ const char *gett_status_string(gett_status_t status);
  * variants), kernel kind ("macro", "stream", "tail", "direct": operands
  * copied from device memory straight into LDS, or "direct-stream": the same,
  * by persistent workgroups that copy the next tile's operands while storing
- * the current tile), K slices, the
+ * the current tile, or "direct-element": copied element by element), K slices, the
  * stream-K tail's whole tiles, workgroups and boxes per workgroup, the
  * partial-tile workspace, grid, the ranked candidates and the flop / byte
  * counts of Eq. 12-14.

@@ -889,6 +889,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                     best.cost = cost;
                 }
             }
+            // Slots beyond the 64 MiB of gett_contract_noalloc have to pay for
+            // being refused there.
+            if (best.tile >= 0 && dtype == GETT_FLOAT32 && elements &&
+                tx * ty * best.slices * tileBytes > 67108864.0)
+                best.cost *= 1.3;
             // (element-wise gathers wait in turn into one LDS buffer; in fp32
             // measured 1.1-1.2 times the model's time, on 128 x 128 x 32
             // 1.2-1.6)
