@@ -687,9 +687,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // wavefronts per SIMD this much of their MFMA rate (odd extents
         // against even ones: 4096^3-shaped 1.1-1.25, C of 529 x 3721 over 3721
         // 1.45 on 32 x 64 tiles).
+        // (an X of few rows is a small part of every tile's gathers)
+        const bool xVec = vecX || (sizeX <= 64 && 16.0 * bytesX < bytesY + bytesC);
         const bool elements =
-            slowGather || !(vecX && (vecY || vecYSplit || kSplitAhead));   // some operand's
-        const double kElementWise = dtype != GETT_FLOAT32 || (vecX && (vecY || vecYSplit)) ||
+            slowGather || !(xVec && (vecY || vecYSplit || kSplitAhead));   // some operand's
+        const double kElementWise = dtype != GETT_FLOAT32 || (xVec && (vecY || vecYSplit)) ||
                                             kSplitAhead
                                         ? 1.0
                                     : c.mt * c.nt <= 32 * 64 ? 1.3
@@ -764,7 +766,10 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const double single =
                 !elements                                             ? 1.0
                 : c.nbuf == 1 || k == 1                               ? 1.4
-                : slowGather && vecX && vecYSplit                     ? 1.0
+                // a column split into single vectors writes C in 16-byte runs
+                // (268 x 256 x 16 over 280 fp32: 42 us 256 wide, 31 on 32 x 64)
+                : slowGather && xVec && vecYSplit
+                    ? (c.nt == 256 && pow2_part(Iy[0].extent) <= VW ? 1.6 : 1.0)
                 : dtype == GETT_FLOAT32 && c.nt == 256 && c.kt == 16  ? (c.mt == 32 ? 1.7 : 2.2)
                 : dtype == GETT_FLOAT32 && wpt == 1                   ? 1.5
                                                                       : 1.0;
