@@ -33,7 +33,9 @@ struct Candidate {
     int tile = 0, kind = 0;                 // kind 0: macro-kernel, 1: streaming kernel,
                                             // 2: macro-kernel over K slices,
                                             // 3: stream-K tail kernel,
-                                            // 4: direct-load kernel
+                                            // 4: direct-load kernel,
+                                            // 5: persistent direct-load kernel,
+                                            // 6: element-wise direct-load kernel
     int slices = 1;                         // workgroups per tile (kind 2), tail
                                             // workgroups (kind 3)
     double tMfma = 0, tMem = 0, cost = 0;   // seconds
@@ -91,7 +93,7 @@ struct gett_plan_s {
     int kind;                // 0: macro-kernel, 1: persistent streaming kernel,
                              // 2: macro-kernel over K slices (desc.kslices > 1),
                              // 3: stream-K tail kernel (desc.tailFull ...),
-                             // 4: direct-load kernel
+                             // 4: direct-load kernel, 5: persistent, 6: element-wise
     std::vector<gett::Candidate> ranked;   // every candidate, best model estimate first
     // the arguments of gett_plan, kept to re-plan with another candidate
     std::string modes[3];
