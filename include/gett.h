@@ -186,8 +186,9 @@ gett_status_t gett_plan(gett_plan_t *plan, gett_dtype_t dtype,
  * ends.  Such a call synchronises `stream` (when buffers grow), and inside a
  * HIP graph capture it is refused: capture a plan's calls after an eager
  * call on the same stream, or use gett_contract_noalloc.  Calls on one stream
- * share its buffers (they run in order); calls on different streams use
- * different ones.  Errors: GETT_ERROR_HIP also when that allocation fails;
+ * share its buffers: they run in order, and the launches of one call are
+ * enqueued together also when several host threads call on that stream; calls
+ * on different streams use different ones.  Errors: GETT_ERROR_HIP also when that allocation fails;
  * GETT_ERROR_NOT_SUPPORTED, with nothing enqueued, when it would have to
  * happen while `stream` is capturing a graph.
  */
@@ -205,8 +206,9 @@ gett_status_t gett_contract(const gett_plan_t plan, double alpha, const void *A,
  * ends: 64 MiB of partial-tile slots and 65536 per-tile counters.  Each call
  * first zeroes the counters its plan uses (a small kernel on `stream`).
  * Every call on one GPU shares that buffer and leaves its contents behind:
- * calls that overlap in time on one GPU (several streams, several host
- * threads) race and must be serialised by the caller, e.g. on one stream.
+ * calls that overlap in time on one GPU (several streams) race and must be
+ * serialised by the caller, e.g. on one stream (from any number of host
+ * threads: the launches of one call are enqueued together).
  *
  * Arguments, pointer rules and asynchrony as for gett_contract.  Errors as
  * for gett_contract, and GETT_ERROR_NOT_SUPPORTED, before any launch, for a

@@ -301,7 +301,7 @@ gett_status_t contract_with(const gett_plan_s &P, double alpha, const void *A, c
     LaunchFn fn = launch_fn(P.dtype, P.tile, xmode, ymode, kind);
     if (!fn) return GETT_ERROR_NOT_SUPPORTED;
     if (inject_launch_fault()) return GETT_ERROR_HIP;
-    Partials part;
+    Partials part;   // holds the workspace until this call's launches are enqueued
     if (kind == 2 || kind == 3) {   // partial tiles, summed through the workspace
         const gett_status_t st = ws(stream, P.wsCounters, P.wsTileBytes, part);
         if (st != GETT_SUCCESS) return st;

@@ -7,7 +7,9 @@
 // library runs on holds one copy of the buffer (kScratchTiles bytes of slots
 // and kScratchCounters counters) until the process ends; every call on that
 // GPU shares it, so calls that overlap in time on one GPU race (serialise
-// them, e.g. on one stream).
+// them, e.g. on one stream).  A call holds the buffer's lock from the clearing
+// of the counters to its last launch, so that calls from several threads on one
+// stream do run one after the other there.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,8 +30,12 @@ static __device__ __align__(256) unsigned char scratch[kScratchTiles + kScratchC
 namespace gett {
 namespace {
 
-std::mutex g_mutex;
-std::map<int, unsigned char *> g_address;   // device -> address of its copy of `scratch`
+struct Scratch {
+    unsigned char *address = nullptr;   // of the device's copy of `scratch`
+    std::mutex use;                     // held by the call that is enqueuing its launches
+};
+std::mutex g_mutex;   // of the map; its entries stay where they are
+std::map<int, Scratch> g_scratch;   // by device
 
 // Zero the first n counters (a kernel, not a memset: the call may be captured
 // into a graph, where memset nodes have misbehaved).
@@ -39,23 +45,23 @@ __global__ void clear_counters(int *counters, unsigned n)
     if (i < n) counters[i] = 0;
 }
 
-// Address of this device's copy of the buffer, looked up on the first call
+// This device's copy of the buffer, its address looked up on the first call
 // made with the device current.
-gett_status_t scratch_address(unsigned char **out)
+gett_status_t scratch_of_device(Scratch **out)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return GETT_ERROR_HIP;
     std::lock_guard<std::mutex> lock(g_mutex);
-    auto it = g_address.find(dev);
-    if (it == g_address.end()) {
+    Scratch &s = g_scratch[dev];
+    if (!s.address) {
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {
             (void)hipGetLastError();
             return GETT_ERROR_HIP;
         }
-        it = g_address.emplace(dev, static_cast<unsigned char *>(p)).first;
+        s.address = static_cast<unsigned char *>(p);
     }
-    *out = it->second;
+    *out = &s;
     return GETT_SUCCESS;
 }
 
@@ -65,9 +71,11 @@ gett_status_t static_workspace(hipStream_t stream, uint64_t counters, uint64_t t
                                Partials &out)
 {
     if (counters > kScratchCounters || tileBytes > kScratchTiles) return GETT_ERROR_NOT_SUPPORTED;
-    unsigned char *base = nullptr;
-    const gett_status_t st = scratch_address(&base);
+    Scratch *own = nullptr;
+    const gett_status_t st = scratch_of_device(&own);
     if (st != GETT_SUCCESS) return st;
+    out.hold = std::unique_lock<std::mutex>(own->use);
+    unsigned char *base = own->address;
     int *ctr = reinterpret_cast<int *>(base + kScratchTiles);
     if (counters > 0) {
         const unsigned n = (unsigned)counters;

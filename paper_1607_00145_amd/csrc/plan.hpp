@@ -3,6 +3,7 @@
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -62,18 +63,23 @@ struct Hooks {
 };
 Hooks read_hooks();
 
-// Workspace of a launch: per-tile counters and partial-tile slots (null when
-// the plan has no partial tiles).
+// Workspace of a call: per-tile counters and partial-tile slots (null when
+// the plan has no partial tiles), and the lock on them.  A call may enqueue
+// several kernels that hand each other the slots; calls on one stream share
+// the buffers, so a call holds them until its last launch is enqueued: no other
+// thread's launch, nor the growth of the buffers, falls between its own.
 struct Partials {
     void *tiles = nullptr;
     int *counters = nullptr;
+    std::unique_lock<std::mutex> hold;
 };
 
 typedef hipError_t (*LaunchFn)(const KDesc &, const void *, const void *, void *, double, double,
                                const Partials &, hipStream_t);
 
-// Device workspace for a launch's partial tiles: `counters` zeroed int32
-// counters and `tileBytes` bytes of slots, filled into `out`.
+// Device workspace for a call's partial tiles: `counters` zeroed int32
+// counters and `tileBytes` bytes of slots, filled into `out` with the lock on
+// them.
 typedef gett_status_t (*WorkspaceFn)(hipStream_t stream, uint64_t counters, uint64_t tileBytes,
                                      Partials &out);
 // The library's own: a pair of buffers per (device, stream), grown on demand.

@@ -28,9 +28,10 @@ struct Buffers {
     uint64_t counterBytes = 0;
     void *tiles = nullptr;
     uint64_t tileBytes = 0;
+    std::mutex use;   // held by the call that is enqueuing its launches
 };
 
-std::mutex g_mutex;
+std::mutex g_mutex;   // of the map; its entries stay where they are
 std::map<std::pair<int, hipStream_t>, Buffers> g_buffers;
 
 uint64_t round_up(uint64_t n) { return (n + 4095) / 4096 * 4096; }
@@ -42,8 +43,13 @@ gett_status_t stream_workspace(hipStream_t stream, uint64_t counters, uint64_t t
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return GETT_ERROR_HIP;
-    std::lock_guard<std::mutex> lock(g_mutex);
-    Buffers &b = g_buffers[{dev, stream}];
+    Buffers *found;
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        found = &g_buffers[{dev, stream}];
+    }
+    Buffers &b = *found;
+    out.hold = std::unique_lock<std::mutex>(b.use);
     const uint64_t cBytes = counters * sizeof(int);
     const bool growC = cBytes > b.counterBytes, growT = tileBytes > b.tileBytes;
     if (growC || growT) {

@@ -66,3 +66,39 @@ def test_same_bits_and_no_alloc(gpu, monkeypatch):
     torch.cuda.synchronize()
     for o in outs[1:]:
         assert torch.equal(o, outs[0])
+
+
+def test_threads_on_one_stream(gpu, monkeypatch):
+    """Four host threads call one plan on one stream, each with its own inputs
+    and C: every C has the bits of the same call made alone.  (The two launches
+    of a call share the stream's slots, so they have to be enqueued together.)"""
+    import threading
+
+    import torch
+
+    monkeypatch.setenv("GETT_FORCE_TILE", "4")
+    monkeypatch.setenv("GETT_FORCE_KSLICES", "14")
+    gen = torch.Generator(device=gpu).manual_seed(6)
+    new = lambda *s: torch.rand(s, generator=gen, device=gpu).permute(*reversed(range(len(s))))
+    sets = [(new(24, 94, 384), new(94, 376, 24)) for _ in range(4)]
+    ref = [torch.zeros((376, 384), device=gpu).t() for _ in sets]
+    p = g.Plan(("a,b", "a,c,d", "d,b,c"), ref[0], *sets[0])
+    assert p.describe()["kslices"] == 14 and p.describe()["tile"]["id"] == 4
+    for (A, B), C in zip(sets, ref):
+        p(A, B, C)
+    outs = [[torch.zeros((376, 384), device=gpu).t() for _ in range(40)] for _ in sets]
+    torch.cuda.synchronize()
+    stream = torch.cuda.current_stream()
+    start = threading.Barrier(len(sets))
+
+    def work(i):
+        start.wait()
+        for C in outs[i]:
+            p(*sets[i], C, stream=stream)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(sets))]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    torch.cuda.synchronize()
+    for i in range(len(sets)):
+        assert all(torch.equal(C, ref[i]) for C in outs[i]), i
