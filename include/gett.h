@@ -264,8 +264,10 @@ const char *gett_status_string(gett_status_t status);
  * copied from device memory straight into LDS, or "direct-stream": the same,
  * by persistent workgroups that copy the next tile's operands while storing
  * the current tile, or "direct-element": copied element by element), K slices, the
- * stream-K tail's whole tiles, workgroups and boxes per workgroup, the
- * partial-tile workspace, grid, the ranked candidates and the flop / byte
+ * stream-K tail's whole tiles, workgroups and boxes per workgroup, how C is
+ * accessed ("c_access": "vector", 16-byte vectors on the 16-byte grid; "run",
+ * vectors at any element address where columns follow one another in C;
+ * "element"), the partial-tile workspace, grid, the ranked candidates and the flop / byte
  * counts of Eq. 12-14.
  * Returns "" for NULL.
  */

@@ -1290,7 +1290,9 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     d.order = streaming ? 1 : 0;
     d.xcdremap = -1;   // decided per call (see gett_contract)
     if (const char *xr = hk.xcdRemap) d.xcdremap = atoi(xr) != 0;   // tuning hook
-    d.cvec = cvec ? 1 : 0;
+    // element-wise where the caller asks for it; a tile whose lanes do not own
+    // VW consecutive columns has no other access
+    d.cvec = cvec ? 1 : (flags & GETT_FLAG_SCALAR) || ts.ry != VW ? -1 : 0;
     d.xscalar_kfast = sX(Ik[0]) < sX(Ix[0]) ? 1 : 0;
     d.yscalar_kfast = sY(Ik[0]) < sY(Iy[0]) ? 1 : 0;
     // Element-wise gathers of an operand that is stride-one along the second
@@ -1414,7 +1416,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     o << ",\"kbox\":{\"kj\":" << kj << ",\"tj\":" << tj << ",\"elements\":" << kbox << ",\"blocks\":" << nblk
       << ",\"steps\":" << nsteps << "}";
     o << ",\"gather_x\":\"" << mode_name(xmode) << "\",\"gather_y\":\"" << mode_name(ymode)
-      << "\",\"c_vector\":" << (cvec ? "true" : "false") << ",\"y_vector_stride\":" << yes
+      << "\",\"c_vector\":" << (cvec ? "true" : "false") << ",\"c_access\":\""
+      << (d.cvec > 0 ? "vector" : d.cvec == 0 ? "run" : "element") << "\"" << ",\"y_vector_stride\":" << yes
       << ",\"c_order_run\":" << crun << ",\"lane_perm\":[" << d.xperm << "," << d.yperm << "]";
     o << ",\"grid\":{\"tiles_x\":" << tilesX << ",\"tiles_y\":" << tilesY << ",\"workgroups\":"
       << tilesX * tilesY << ",\"threads\":" << ts.wm * ts.wn * 64 << "}";

@@ -279,7 +279,7 @@ gett_status_t contract_with(const gett_plan_s &P, double alpha, const void *A, c
     // 16-byte vector accesses need 16-byte aligned base pointers.
     if (xmode != kGatherScalar && ((uintptr_t)X % 16)) xmode = kGatherScalar;
     if (ymode != kGatherScalar && ((uintptr_t)Y % 16)) ymode = kGatherScalar;
-    if (d.cvec && ((uintptr_t)C % 16)) d.cvec = 0;
+    if (d.cvec > 0 && ((uintptr_t)C % 16)) d.cvec = 0;
     // Tile walk across the XCDs: consecutive tiles on one XCD suits the
     // compute-bound and write-only walks; a read-modify-write C stream
     // (streaming walk, beta != 0) runs faster in hardware order (measured).

@@ -409,7 +409,7 @@ __device__ __forceinline__ void direct_tile(const KDesc &d, const T *__restrict_
                 for (int r = 0; r < 4; ++r)
                     W[(size_t)(((a * WT::CB + b) * 4 + r) * NTH + tid)] = w.acc[a][b][r];
     } else {
-        w.template unpack<1>(Ct, offCx, offCy, alpha, beta, d.cvec != 0);
+        w.template unpack<1>(Ct, offCx, offCy, alpha, beta, d.cvec);
     }
 }
 
@@ -714,7 +714,7 @@ gett_element_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict_
 #pragma unroll
         for (int grp = 0; grp < NG; ++grp) mma(fx[grp], fy[grp]);
     }
-    w.template unpack<1>(C + (tb.cx + tb.cy), offCx, offCy, alpha, beta, d.cvec != 0);
+    w.template unpack<1>(C + (tb.cx + tb.cy), offCx, offCy, alpha, beta, d.cvec);
 }
 
 // Persistent direct-load kernel for plans whose contracted set is one K box.
@@ -836,7 +836,7 @@ gett_direct_stream_kernel(const KDesc d, const T *__restrict__ X, const T *__res
         w.zero();
 #pragma unroll
         for (int grp = 0; grp < NG; ++grp) mma(fx[grp], fy[grp]);
-        w.template unpack<1, WHOLE>(Ct, offCx[cur], offCy[cur], alpha, beta, d.cvec != 0);
+        w.template unpack<1, WHOLE>(Ct, offCx[cur], offCy[cur], alpha, beta, d.cvec);
         if (!more) break;
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");

@@ -760,7 +760,7 @@ struct WaveTile {
     // so every wavefront issues every store).
     template <int PARTS = 1, bool ALL = false>
     __device__ __forceinline__ void unpack(T *__restrict__ C, const int *offCx, const int *offCy,
-                                           T alpha, T beta, bool cvec) const
+                                           T alpha, T beta, int cvec) const
     {
         static_assert(NR % PARTS == 0, "row parts");
         constexpr int NP = NR / PARTS;
@@ -769,7 +769,7 @@ struct WaveTile {
         for (int grp = 0; grp < RB / RX; ++grp) {
             int ox[NR];
             rows_of(offCx, grp, ox);
-            if (kVecC && cvec) {
+            if (kVecC && cvec > 0) {
                 int oy[CGV];
                 cols_vec(offCy, oy);
 #pragma unroll
@@ -802,11 +802,12 @@ struct WaveTile {
                         }
                 }
             } else if constexpr (kVecC) {
-                // C off the 16-byte grid (odd extents, strides or base): a
-                // lane's VW columns are still one vector where they follow
-                // one another in C -- device memory takes 16-byte accesses at
-                // any element address -- and single elements only where a
-                // group is cut by the end of a run or of C.
+                // C off the 16-byte grid (odd extents, strides or base;
+                // cvec 0): a lane's VW columns are still one vector where
+                // they follow one another in C -- device memory takes 16-byte
+                // accesses at any element address -- and single elements only
+                // where a group is cut by the end of a run or of C.  cvec < 0
+                // (the caller asked for element-wise accesses): all single.
                 typedef vec uvec __attribute__((aligned(sizeof(T))));
                 int oy[CB];
                 bool run[CGV];
@@ -814,7 +815,7 @@ struct WaveTile {
                 for (int cg = 0; cg < CGV; ++cg) {
 #pragma unroll
                     for (int j = 0; j < VW; ++j) oy[cg * VW + j] = offCy[col_of(cg) + j];
-                    run[cg] = oy[cg * VW] >= 0;
+                    run[cg] = cvec == 0 && oy[cg * VW] >= 0;
 #pragma unroll
                     for (int j = 1; j < VW; ++j)
                         run[cg] = run[cg] && oy[cg * VW + j] == oy[cg * VW] + j;
@@ -1217,14 +1218,14 @@ gett_macro_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__ 
         }
         }
         if constexpr (CORDER && WT::kVecC && !kPartials) {   // compiled only into the tiles that carry it
-            if (d.crun > 0 && d.cvec) {
+            if (d.crun > 0 && d.cvec > 0) {
                 const int cols = (int)min((int64_t)d.stepY, d.sizeY - (int64_t)ty * d.stepY);
                 unpack_c_order<T, MT, NTH>(w, Ct, panels, kPanels, offCx, offCy, cols, d.crun,
                                            d.piecesInv, alpha, beta, tid);
                 return;
             }
         }
-        w.template unpack<ONEBOX ? 2 : 1>(Ct, offCx, offCy, alpha, beta, d.cvec != 0);
+        w.template unpack<ONEBOX ? 2 : 1>(Ct, offCx, offCy, alpha, beta, d.cvec);
     };
 
     if constexpr (TAIL) {
@@ -1381,7 +1382,7 @@ gett_stream_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
             gx.load(X + (nb.x + ox0), lim);
             gy.load(Y + (nb.y + oy0), lim);
         }
-        w.template unpack<2>(C + (cb.cx + cb.cy), offCx[cur], offCy[cur], alpha, beta, d.cvec != 0);
+        w.template unpack<2>(C + (cb.cx + cb.cy), offCx[cur], offCy[cur], alpha, beta, d.cvec);
         cb = nb;
         if (!more) break;
         if (withK) {

@@ -150,6 +150,22 @@ def test_flags_change_the_plan():
     assert d2["gather_x"] == d2["gather_y"] == "scalar" and d2["c_vector"] is False
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_scalar_flag_means_element_wise_c(dtype, monkeypatch):
+    """GETT_FLAG_SCALAR: C is accessed in single elements by every tile and
+    layout, also where its columns follow one another off the 16-byte grid (C
+    there is accessed in vectors at element alignment without the flag)."""
+    code, vw = (g.GETT_FLOAT32, 4) if dtype == "f32" else (g.GETT_FLOAT64, 2)
+    for tile in range(10 if dtype == "f32" else 15):
+        monkeypatch.setenv("GETT_FORCE_TILE", str(tile))
+        for m in (64, 67):
+            d = [describe("m,n", "m,k", "k,n", {"m": m, "n": 40, "k": 30}, dtype=code, flags=f)
+                 for f in (0, g.GETT_FLAG_SCALAR)]
+            wide = d[0]["tile"]["reads"][1] == vw   # the lanes own whole vectors of columns
+            assert d[0]["c_access"] == ("element" if not wide else "run" if m % vw else "vector")
+            assert d[1]["c_access"] == "element" and d[1]["c_vector"] is False
+
+
 def test_kbox_covers_contracted_set():
     """K boxes tile the contracted index space: steps * box >= S_Ik with the
     block split of one index (index reinterpretation, Sec. 3.2.1)."""
