@@ -1406,7 +1406,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     }
     o << "]";
     o << ",\"streaming\":" << (streaming ? "true" : "false");
-    o << ",\"kernel\":\"" << (kind == 2 ? "macro" : kind_name(kind))
+    const bool onDirect = kind == 2 && direct_slices(ts.deff > 0.0f, xmode, ymode);
+    o << ",\"kernel\":\"" << (onDirect ? "direct" : kind == 2 ? "macro" : kind_name(kind))
       << "\",\"kslices\":" << kslices;
     o << ",\"tail\":{\"full_tiles\":" << d.tailFull << ",\"workgroups\":" << d.tailWgs
       << ",\"boxes\":" << d.tailLen << "}";
@@ -1417,7 +1418,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
       << ",\"steps\":" << nsteps << "}";
     o << ",\"gather_x\":\"" << mode_name(xmode) << "\",\"gather_y\":\"" << mode_name(ymode)
       << "\",\"c_vector\":" << (cvec ? "true" : "false") << ",\"c_access\":\""
-      << (d.cvec > 0 ? "vector" : d.cvec == 0 ? "run" : "element") << "\"" << ",\"y_vector_stride\":" << yes
+      << (onDirect || d.cvec < 0 ? "element" : d.cvec > 0 ? "vector" : "run") << "\"" << ",\"y_vector_stride\":" << yes
       << ",\"c_order_run\":" << crun << ",\"lane_perm\":[" << d.xperm << "," << d.yperm << "]";
     o << ",\"grid\":{\"tiles_x\":" << tilesX << ",\"tiles_y\":" << tilesY << ",\"workgroups\":"
       << tilesX * tilesY << ",\"threads\":" << ts.wm * ts.wn * 64 << "}";

@@ -85,8 +85,7 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
             static_cast<T>(alpha), static_cast<T>(beta), static_cast<T *>(nullptr), nullptr);
     } else if constexpr (KIND == 2) {
         if (d.kslices < 2 || d.tile0 != 0) return hipErrorInvalidValue;
-        if constexpr (t.deff > 0.0f && direct_modes(XM, YM)) {
-            // tiles that carry the direct-load kernel slice on it
+        if constexpr (direct_slices(t.deff > 0.0f, XM, YM)) {
             const bool whole = d.kbox == t.kt && d.k()[d.kj].ext % d.tj == 0;
             constexpr auto kWhole = gett_direct_slice_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx,
                                                              t.ry, XM, YM, true>;
@@ -105,14 +104,14 @@ hipError_t launch_one(const KDesc &d, const void *X, const void *Y, void *C, dou
                 dim3(tiles * blocks), dim3(threads), 0, stream, d,
                 static_cast<const T *>(w.tiles), static_cast<T *>(C), static_cast<T>(alpha),
                 static_cast<T>(beta));
-            return hipGetLastError();
+        } else {
+            hipLaunchKernelGGL(
+                (gett_macro_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, t.wpe, t.pf, t.nbuf, XM,
+                                   YM, t.onebox, t.corder, 0, 1>),
+                dim3(tiles * (unsigned)d.kslices), dim3(threads), 0, stream, d,
+                static_cast<const T *>(X), static_cast<const T *>(Y), static_cast<T *>(C),
+                static_cast<T>(alpha), static_cast<T>(beta), static_cast<T *>(w.tiles), w.counters);
         }
-        hipLaunchKernelGGL(
-            (gett_macro_kernel<T, t.mt, t.nt, t.kt, t.wm, t.wn, t.rx, t.ry, t.wpe, t.pf, t.nbuf, XM,
-                               YM, t.onebox, t.corder, 0, 1>),
-            dim3(tiles * (unsigned)d.kslices), dim3(threads), 0, stream, d,
-            static_cast<const T *>(X), static_cast<const T *>(Y), static_cast<T *>(C),
-            static_cast<T>(alpha), static_cast<T>(beta), static_cast<T *>(w.tiles), w.counters);
     } else if constexpr (KIND == 3) {
         if (d.tailFull < 0 || d.tailWgs < 1 || d.tailLen < 1 || (unsigned)d.tailFull >= tiles ||
             (uint64_t)d.tailWgs * (uint64_t)d.tailLen <

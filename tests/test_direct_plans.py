@@ -65,6 +65,21 @@ def test_vector_index_block_length(k, tj, blocks):
     assert (d["kbox"]["tj"], d["kbox"]["blocks"]) == (tj, blocks)
 
 
+@pytest.mark.parametrize("tile", sorted(DIRECT_TILES))
+def test_slices_run_the_direct_kernel_on_plain_vectors_only(monkeypatch, tile):
+    """K slices of a tile that carries the direct-load kernel: on it when both
+    operands gather in plain vectors, on the macro-kernel after a K split
+    (strided vectors of Y) and for element-wise gathers."""
+    monkeypatch.setenv("GETT_FORCE_TILE", str(tile))
+    monkeypatch.setenv("GETT_FORCE_KSLICES", "4")
+    d = describe(("a,b", "a,c,d", "d,b,c"), {"a": 384, "b": 376, "c": 40, "d": 384})
+    assert d["kslices"] == 4 and d["kernel"] == "direct" and d["c_access"] == "element"
+    d = describe(("a,b", "k,l,a", "l,k,b"), {"a": 384, "b": 376, "k": 64, "l": 64})
+    assert d["kslices"] == 4 and d["gather_y"] == "k-vector-strided" and d["kernel"] == "macro"
+    d = describe(("a,b", "a,k", "k,b"), {"a": 383, "b": 375, "k": 4097})
+    assert d["kslices"] == 4 and d["gather_x"] == "scalar" and d["kernel"] == "macro"
+
+
 def test_write_only_6d_workload_runs_the_persistent_kernel():
     w = wl.BY_NAME["ccsdt6_fp64"]
     d = describe((w.modes_C, w.modes_A, w.modes_B), w.extents, g.GETT_FLOAT64)

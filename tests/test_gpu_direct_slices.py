@@ -29,12 +29,39 @@ def test_direct_slices(gpu, monkeypatch, dtype, tile, name, slices):
     modes, ext = CASES[name]
     d = describe(modes, ext, dtype)
     assert d["kslices"] == slices and d["gather_x"] in ("row-vector", "k-vector")
+    assert d["kernel"] == "direct"
     assert d["gather_y"] in ("row-vector", "k-vector")
     rng = np.random.default_rng(slices + len(name) + int(tile))
     for alpha, beta in [(1.0, 0.0), (-0.5, 1.5), (0.0, 2.0)]:
         check_case(gpu, rng, modes, shapes(modes, ext), dtype, alpha, beta)
     check_case(gpu, rng, modes, shapes(modes, ext), dtype, 1.0, 0.5, offsets=(1, 0, 0))
     check_case(gpu, rng, modes, shapes(modes, ext), dtype, 1.0, 0.5, offsets=(0, 1, 0))
+    got, ref = check_case(gpu, rng, modes, shapes(modes, ext), dtype, 1.0, 1.0, dist="int")
+    np.testing.assert_array_equal(got.astype(np.float64), ref.out64)
+
+
+SPLIT = {   # operands stride-one along different contracted indices
+    "ab-kla-lkb": (("a,b", "k,l,a", "l,k,b"), {"a": 132, "b": 260, "k": 48, "l": 40}),
+    "ab-klma-lmkb": (("a,b", "k,l,m,a", "l,m,k,b"), {"a": 256, "b": 140, "k": 24, "l": 20, "m": 5}),
+}
+
+
+@pytest.mark.parametrize("slices", [2, 7])
+@pytest.mark.parametrize("name", list(SPLIT))
+@pytest.mark.parametrize("dtype,tile", DIRECT_TILES, ids=IDS)
+def test_slices_after_a_k_split(gpu, monkeypatch, dtype, tile, name, slices):
+    """Strided vectors of Y: the same tiles' slices on the macro-kernel, which
+    start inside the split indices and end in partial blocks (l = 20 or 40
+    against boxes of 8 by 4)."""
+    monkeypatch.setenv("GETT_FORCE_TILE", tile)
+    monkeypatch.setenv("GETT_FORCE_KSLICES", str(slices))
+    modes, ext = SPLIT[name]
+    d = describe(modes, ext, dtype)
+    assert d["kslices"] == slices and d["gather_y"] == "k-vector-strided"
+    assert d["y_vector_stride"] > 1 and d["kernel"] == "macro"
+    rng = np.random.default_rng(slices + 17 * int(tile))
+    for alpha, beta in [(1.0, 0.0), (-0.5, 1.5)]:
+        check_case(gpu, rng, modes, shapes(modes, ext), dtype, alpha, beta)
     got, ref = check_case(gpu, rng, modes, shapes(modes, ext), dtype, 1.0, 1.0, dist="int")
     np.testing.assert_array_equal(got.astype(np.float64), ref.out64)
 

@@ -30,6 +30,9 @@ MODES = {"row-vector": 0, "k-vector": 1, "scalar": 2, "row-vector-strided": 3,
 BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
 NAME = re.compile(r"_ZN4gett17gett_macro_kernelI([fd])((?:Li\d+E)+)EEv")
 DIRECT = re.compile(r"_ZN4gett18gett_direct_kernelI([fd])((?:Li\d+E)+)Lb([01])EEEv")
+DSLICE = re.compile(r"_ZN4gett24gett_direct_slice_kernelI([fd])((?:Li\d+E)+)Lb([01])EEEv")
+SUM = re.compile(r"_ZN4gett22gett_sum_slices_kernelI([fd])((?:Li\d+E)+)EEv")
+ELEMENT = re.compile(r"_ZN4gett19gett_element_kernelI([fd])((?:Li\d+E)+)Lb([01])ELb([01])EEEv")
 DSTREAM = re.compile(r"_ZN4gett25gett_direct_stream_kernelI([fd])((?:Li\d+E)+)Lb([01])EEEv")
 TAIL_SCRATCH_BUDGET = 64   # bytes per lane
 
@@ -62,8 +65,9 @@ def code_objects(lib):
 @pytest.fixture(scope="module")
 def kernels():
     """(type, template integer arguments) -> (scratch bytes per lane, VGPRs)
-    for every gett_macro_kernel instantiation in the library; ("direct" or
-    "dstream", type, arguments + (WHOLE,)) for the direct-load kernels."""
+    for every gett_macro_kernel instantiation in the library; ("direct",
+    "dstream", "dslice", "sum" or "element", type, arguments + the boolean
+    ones) for the direct-load kernels and their sum."""
     if not os.path.exists(f"{LLVM}/llvm-readelf"):
         pytest.skip("llvm-readelf not found")
     res = {}
@@ -75,17 +79,17 @@ def kernels():
             notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", path], check=True,
                                    capture_output=True, text=True).stdout
             for blk in notes.split("\n  - ")[1:]:
-                m, kind = NAME.search(blk), "macro"
-                if not m:
-                    m, kind = DIRECT.search(blk), "direct"
-                if not m:
-                    m, kind = DSTREAM.search(blk), "dstream"
-                if not m:
+                for pattern, kind in ((NAME, "macro"), (DIRECT, "direct"), (DSTREAM, "dstream"),
+                                      (DSLICE, "dslice"), (SUM, "sum"), (ELEMENT, "element")):
+                    m = pattern.search(blk)
+                    if m:
+                        break
+                else:
                     continue
                 field = lambda key: int(re.search(rf"\.{key}:\s+(\d+)", blk).group(1))
                 args = tuple(int(x) for x in re.findall(r"Li(\d+)E", m.group(2)))
                 key = ((m.group(1), args) if kind == "macro" else
-                       (kind, m.group(1), args + (int(m.group(3)),)))
+                       (kind, m.group(1), args + tuple(int(x) for x in m.groups()[2:])))
                 res[key] = (field("private_segment_fixed_size"), field("vgpr_count"))
     finally:
         shutil.rmtree(tmp)
@@ -110,7 +114,8 @@ def plan_kernel(w, kernels):
     t = d["tile"]
     T = "f" if w.dtype == "f32" else "d"
     if d["kernel"] in ("direct", "direct-stream"):
-        kind = "direct" if d["kernel"] == "direct" else "dstream"
+        kind = ("dstream" if d["kernel"] == "direct-stream" else
+                "dslice" if d["kslices"] > 1 else "direct")
         args = (t["mt"], t["nt"], t["kt"], t["waves"][0], t["waves"][1], t["reads"][0],
                 t["reads"][1], MODES[d["gather_x"]], MODES[d["gather_y"]])
         both = [kernels.get((kind, T, args + (whole,))) for whole in (0, 1)]
@@ -155,6 +160,24 @@ def test_direct_kernels_keep_two_wavefronts_per_simd(kernels):
     direct.update(dstream)
     for key, (scratch, vgprs) in direct.items():
         assert scratch == 0 and vgprs <= 256, (key, scratch, vgprs)
+
+
+def test_slices_and_elements_keep_two_wavefronts_per_simd(kernels):
+    """The K slices of the direct-load tiles (vector gathers of both operands,
+    whole and partial boxes), the kernel that sums them and the element-wise
+    direct-load kernel (lanes along either index of either operand): no
+    spills, at most 256 VGPRs.  Tiles whose slices run on the direct-load
+    kernel carry no macro-kernel for them."""
+    tiles = {k[2][:7] for k in kernels if k[0] == "direct"}
+    assert len(tiles) == 3
+    count = {kind: [k for k in kernels if k[0] == kind] for kind in ("dslice", "sum", "element")}
+    assert {k: len(v) for k, v in count.items()} == {"dslice": 3 * 4 * 2, "sum": 3, "element": 3 * 4}
+    for key in sum(count.values(), []):
+        scratch, vgprs = kernels[key]
+        assert scratch == 0 and vgprs <= 256, (key, scratch, vgprs)
+    dead = [k for k in kernels if len(k) == 2 and k[0] == "f" and k[1][:7] in tiles
+            and k[1][15] == 1 and max(k[1][10:12]) <= MODES["k-vector"]]
+    assert not dead, dead
 
 
 def test_compute_bound_fp32_workload_runs_direct(kernels):
