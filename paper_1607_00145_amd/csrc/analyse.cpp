@@ -26,6 +26,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <limits>
 #include <cctype>
 #include <new>
 #include <sstream>
@@ -637,17 +638,29 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         cRunY = Iy[0].extent;
         for (size_t i = 1; i < Iy.size() && Iy[i].strC == cRunY; ++i) cRunY *= Iy[i].extent;
     }
-    // Every (tile, kernel kind) pair is a candidate; the model ranks them.
+    // The longest chain a candidate may sum in and still rank ahead (below).
+    double maxChain = std::numeric_limits<double>::infinity();
+    auto keeps = [&](const Candidate &c) { return c.chain <= maxChain; };
+    auto better = [&](const Candidate &a, const Candidate &b) {
+        if (b.tile < 0 || keeps(a) != keeps(b)) return b.tile < 0 || keeps(a);
+        return a.cost < b.cost;
+    };
+    // Every (tile, kernel kind) pair is a candidate; the model ranks them,
+    // either by what they cost with the gathers the operands allow (`gathers`)
+    // or, for the reference below, as if every tile gathered alike.
+    auto candidates = [&](bool gathers) {
     std::vector<Candidate> ranked;
     for (int t = 0; t < num_tiles(dtype); ++t) {
         const TileShape &c = tile_shape(dtype, t);
+        if (!gathers && c.nt >= 8 * c.mt) continue;   // the tile for few rows: by its gathers only
         const double tileBytes = (double)c.mt * c.nt * itemB;
         // a one-box tile is ranked only for a contracted set in one box whose
         // operands are both gathered in vectors: it waits for each operand's
         // gathers in turn, which element-wise gathers make long (it still
         // runs any plan it is forced onto)
-        if (c.onebox && (box_for(c.kt).nsteps > 1 || slowGather || !(vecX && vecY)) && !(ft && atoi(ft) == t) &&
-            !(force && force->tile == t))
+        if (c.onebox &&
+            (box_for(c.kt).nsteps > 1 || slowGather || (gathers && !(vecX && vecY))) &&
+            !(ft && atoi(ft) == t) && !(force && force->tile == t))
             continue;
         std::vector<Index> ksplit;
         const bool kSplitAhead = k_split(c.kt, ksplit) > 0;
@@ -670,6 +683,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                       std::ceil(wpt / 4.0)
                 : perSimd;
         const double kpad = (double)std::max<int64_t>(b.nsteps, 1) * c.kt;
+        const double oneChain = 0.25 * (double)an.sizeK;
+        const double boxChain = oneChain / (double)std::max<int64_t>(b.nsteps, 1);
         const double waveFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * kpad * 2.0;
         // A K split gathers both operands in 16-byte runs whose cache lines
         // return late: a single LDS buffer waits for them (1.4), and so does a
@@ -678,21 +693,22 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // 17.7 ms, the 128 x 256 x 32 tile with two wavefronts per SIMD
         // 10.5 ms), and the more so a box of 16 fp32 positions, 16-byte runs
         // of both operands (the same contractions: over 21 ms on 128 x 128 x 16).
-        const double kSplitWait = !kSplitAhead || b.nsteps <= 1         ? 1.0
-                                  : c.nbuf == 1                         ? 1.4
-                                  : dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.2
-                                  : c.wpe == 1                          ? 1.7
-                                                                        : 1.0;
+        const double kSplitWait =
+            !kSplitAhead || b.nsteps <= 1                      ? 1.0
+            : c.nbuf == 1                                      ? 1.4
+            : gathers && dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.2
+            : c.wpe == 1                                       ? 1.7
+                                                               : 1.0;
         // Element-wise gathers cost an fp32 macro-kernel's one or two
         // wavefronts per SIMD this much of their MFMA rate (odd extents
         // against even ones: 4096^3-shaped 1.1-1.25, C of 529 x 3721 over 3721
         // 1.45 on 32 x 64 tiles).
         // (an X of few rows is a small part of every tile's gathers)
         const bool xVec = vecX || (sizeX <= 64 && 16.0 * bytesX < bytesY + bytesC);
-        const bool elements =
-            slowGather || !(xVec && (vecY || vecYSplit || kSplitAhead));   // some operand's
-        const double kElementWise = dtype != GETT_FLOAT32 || (xVec && (vecY || vecYSplit)) ||
-                                            kSplitAhead
+        const bool elements =   // some operand's
+            gathers && (slowGather || !(xVec && (vecY || vecYSplit || kSplitAhead)));
+        const double kElementWise = !gathers || dtype != GETT_FLOAT32 ||
+                                            (xVec && (vecY || vecYSplit)) || kSplitAhead
                                         ? 1.0
                                     : c.mt * c.nt <= 32 * 64 ? 1.3
                                     : c.wpe == 1             ? 1.2
@@ -701,7 +717,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // the split: one of them takes another cache line per element, the
         // more boxes, the more often (fp32, 53 x 51 x 50 x 49 over 47 x 45:
         // 128 x 128 x 16 tiles 810 us, 256 x 128 x 32 element-wise 554).
-        const bool crossed = !kSplitAhead && splitXK >= 0 && splitYK >= 0 && splitXK != splitYK;
+        const bool crossed = gathers && !kSplitAhead && splitXK >= 0 && splitYK >= 0 && splitXK != splitYK;
         const double kCrossed = crossed && dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.0 : 1.0;
         const double tMfma =
             perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait * kElementWise * kCrossed;
@@ -712,7 +728,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // that for two 128 x 128 direct workgroups; C in single elements
         // takes two to three times that).
         const double rounds = std::ceil(tx * ty / 256.0);
-        const double macroSetup = dtype != GETT_FLOAT32      ? 0.0
+        const double macroSetup = !gathers || dtype != GETT_FLOAT32 ? 0.0
                                   : wpt >= 8                 ? rounds * (vecC ? 8.0e-6 : 16.0e-6)
                                   : c.wpe == 1 && wpt >= 4 ? rounds * (vecC ? 4.0e-6 : 12.0e-6)
                                                            : 0.0;
@@ -749,7 +765,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * bwFrac) *
-                                (dtype != GETT_FLOAT64                  ? 1.0
+                                (!gathers || dtype != GETT_FLOAT64      ? 1.0
                                  : c.nbuf == 1 && b.nsteps > 1          ? 1.4
                                  : elements && c.mt * c.nt <= 32 * 64 ? 1.25
                                                                       : 1.0);
@@ -764,7 +780,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // box: 2.2, 1.7 with more workgroups per CU on 32 rows; one
             // wavefront alone on 64 x 64 1.5)
             const double single =
-                !elements                                             ? 1.0
+                !gathers ? (slowGather && (c.nbuf == 1 || k == 1) ? 1.4 : 1.0)
+                : !elements                                           ? 1.0
                 : c.nbuf == 1 || k == 1                               ? 1.4
                 // a column split into single vectors writes C in 16-byte runs
                 // (268 x 256 x 16 over 280 fp32: 42 us 256 wide, 31 on 32 x 64)
@@ -773,6 +790,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 : dtype == GETT_FLOAT32 && c.nt == 256 && c.kt == 16  ? (c.mt == 32 ? 1.7 : 2.2)
                 : dtype == GETT_FLOAT32 && wpt == 1                   ? 1.5
                                                                       : 1.0;
+            cd.chain = oneChain;
             cd.cost = bound(std::max(tMfma, tMem), tChain) * single + macroSetup;
             ranked.push_back(cd);
         }
@@ -783,24 +801,27 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // along theirs; nothing is staged in registers, so the split's late
         // lines cost no wait beyond the copy's (kSplitWait).
         if (c.deff > 0.0f && !(flags & GETT_FLAG_SCALAR) && b.nsteps >= 1 &&
-            (kSplitAhead ? aligned(Ix, sX, -1) : vecX && vecY)) {
+            (!gathers      ? !slowGather && !kSplitAhead
+             : kSplitAhead ? aligned(Ix, sX, -1)
+                           : vecX && vecY)) {
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw * cuShare);
             Candidate cd;
             cd.tile = t;
             cd.kind = 4;
+            cd.chain = oneChain;
             cd.tMfma = tMfma / kSplitWait * c.eff / c.deff;
             cd.tMem = tMem;
-            cd.cost = bound(std::max(cd.tMfma, tMem), tChain) + tileSetup;
+            cd.cost = bound(std::max(cd.tMfma, tMem), tChain) + (gathers ? tileSetup : 0.0);
             ranked.push_back(cd);
         }
         // The same kernel with element-wise copies, for operands that do not
         // both gather in vectors (fp32): the boxes run over the linearised
         // contracted set, so only the last one is padded, and offsets within
         // an operand take 32 bits.
-        if (c.deff > 0.0f && dtype == GETT_FLOAT32 && !(vecX && vecY) && !kSplitAhead &&
-            !an.emptySum && an.sizeK < INT32_MAX / 2 && an.maxOffA < INT32_MAX &&
+        if (gathers && c.deff > 0.0f && dtype == GETT_FLOAT32 && !(vecX && vecY) &&
+            !kSplitAhead && !an.emptySum && an.sizeK < INT32_MAX / 2 && an.maxOffA < INT32_MAX &&
             an.maxOffB < INT32_MAX) {
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
@@ -809,6 +830,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             Candidate cd;
             cd.tile = t;
             cd.kind = 6;
+            cd.chain = oneChain;
             cd.tMfma = tMfma * boxes * c.kt / kpad / kElementWise * c.eff /
                        (wpt >= 8 ? 0.71 : 0.68) * (crossed && c.mt < 256 ? 1.4 : 1.0);
             cd.tMem = tMem;
@@ -822,7 +844,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // slower than the macro-kernel on the fp64 6D contractions of
         // Appendix A whose y set leads with one index of 24, 3-5% faster
         // on those whose y set leads with a merged run of 384).
-        if (c.dsbw > 0.0f && vecX && vecY && !kSplitAhead && b.nsteps == 1) {
+        if (c.dsbw > 0.0f && (gathers ? vecX && vecY : !slowGather) && !kSplitAhead &&
+            b.nsteps == 1) {
             const double dbw = cRunY >= c.nt ? c.dsbw : c.bw;
             const double tMem = (bytesC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
@@ -830,6 +853,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             Candidate cd;
             cd.tile = t;
             cd.kind = 5;
+            cd.chain = oneChain;
             cd.tMfma = tMfma;
             cd.tMem = tMem;
             cd.cost = bound(std::max(tMfma, tMem), tChain);
@@ -852,20 +876,24 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // Tiles that carry the direct-load kernel slice on it (both operands
             // in vectors): its MFMA rate, the slots summed by a second launch
             // (6 us), as many slices as fill the workgroups the CUs hold at
-            // once (two of 128 x 128, one of eight wavefronts), and a
-            // workspace within the 64 MB of gett_contract_noalloc.
-            const bool directSlices =
-                c.deff > 0.0f && vecX && vecY && !kSplitAhead && !(flags & GETT_FLAG_SCALAR);
+            // once (two of 128 x 128, one of eight wavefronts) or twice that
+            // many (half the chain), and a workspace within the 64 MiB of
+            // gett_contract_noalloc.  A C of 384 x 376 over 144384: 334 us in
+            // 56 slices, 9.2e-7 of the result's norm; 341 us in 113, 6.7e-7
+            // (64 x 64 tiles of the macro-kernel in 64: 439 us, 8.6e-7).
+            const bool directSlices = gathers && c.deff > 0.0f && vecX && vecY && !kSplitAhead;
             std::vector<int> counts;
             for (int P = 2; P <= 256; P *= 2) counts.push_back(P);
             if (directSlices) {
                 counts.clear();
                 const double resident = wpt >= 8 ? 256.0 : 512.0;
-                if (resident / (tx * ty) >= 2.0) counts.push_back((int)(resident / (tx * ty)));
+                if (resident / (tx * ty) >= 2.0)
+                    for (int fill = 1; fill <= 2; ++fill)
+                        counts.push_back((int)(fill * resident / (tx * ty)));
             }
             for (int P : counts) {
                 if (b.nsteps / P < 8) continue;
-                if (directSlices && tx * ty * P * tileBytes > 64.0e6) continue;
+                if (directSlices && tx * ty * P * tileBytes > 67108864.0) continue;
                 const double wgs = tx * ty * P;
                 const double perSimdP =
                     wpt >= 4 ? cu_time((int)tail_occupancy(c, itemB), (int)std::ceil(wgs / 256.0),
@@ -884,15 +912,15 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                     tx * ty * tileBytes * 2.0 * P / kPartialBw +
                     (directSlices ? 6.0e-6 : P * tileBytes / kSumBw + 1.0e-6);
                 const double tChainP = chain(wgs, std::ceil((double)b.nsteps / P));
-                const double cost = bound(std::max(tM, tMemP), tChainP) + tPart;
-                if (best.tile < 0 || cost < best.cost) {
-                    best.tile = t;
-                    best.kind = 2;
-                    best.slices = P;
-                    best.tMfma = tM;
-                    best.tMem = tMemP;
-                    best.cost = cost;
-                }
+                Candidate cd;
+                cd.tile = t;
+                cd.kind = 2;
+                cd.slices = P;
+                cd.chain = std::ceil((double)b.nsteps / P) * boxChain + P;
+                cd.tMfma = tM;
+                cd.tMem = tMemP;
+                cd.cost = bound(std::max(tM, tMemP), tChainP) + tPart;
+                if (better(cd, best)) best = cd;
             }
             // Slots beyond the 64 MiB of gett_contract_noalloc have to pay for
             // being refused there.
@@ -930,7 +958,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const int occ = (int)tail_occupancy(c, itemB);
             const double boxFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * c.kt * 2.0;
             const double boxTime =
-                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) * kSplitWait * kElementWise *
+                std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) *
+                (gathers ? kSplitWait : kSplitAhead && c.nbuf == 1 ? 1.4 : 1.0) * kElementWise *
                 kCrossed * (elements && c.nbuf == 1 ? 2.5 : 1.0);   // spills (element-wise gathers in the
                                                          // piece loop: 869 against 339 us on a C
                                                          // of 529 x 3721 over 3721)
@@ -948,34 +977,24 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 const double tM = units * boxTime;
                 const double tPart = (double)(ntile - ts.full + ts.wgs) * tileBytes * 2.0 / 6.8e12 +
                                      pieces * tileBytes / kSumBw + 1.0e-6;
-                const double cost = bound(std::max(tM, tMem), tChain) + tPart;
-                if (best.tile < 0 || cost < best.cost) {
-                    best.tile = t;
-                    best.kind = 3;
-                    best.slices = 256 * g;
-                    best.tMfma = tM;
-                    best.tMem = tMem;
-                    best.cost = cost;
-                }
+                Candidate cd;
+                cd.tile = t;
+                cd.kind = 3;
+                cd.slices = 256 * g;
+                cd.chain = (ts.full * oneChain +
+                            (ntile - ts.full) * (double)std::min(ts.len, (int64_t)b.nsteps) *
+                                boxChain) /
+                           ntile;
+                cd.tMfma = tM;
+                cd.tMem = tMem;
+                cd.cost = bound(std::max(tM, tMem), tChain) + tPart;
+                if (better(cd, best)) best = cd;
             }
             if (best.tile >= 0) ranked.push_back(best);
         }
     }
-    // K slices also sum in shorter chains: over 3721 positions 4e-7 of the
-    // result's norm against 1.1e-6 in one chain (fp32).  A long contracted set
-    // that is sliced by the other kernels stays so beside the direct-load
-    // kernels of element-wise and split operands, which take it in one.
-    if (an.sizeK > 3000) {
-        const Candidate *other = nullptr;
-        for (const Candidate &c : ranked)
-            if (c.kind <= 3 && (!other || c.cost < other->cost)) other = &c;
-        if (other && other->kind == 2) {
-            const double floor = other->cost * 1.01;
-            for (Candidate &c : ranked)
-                if (c.kind == 6 || (c.kind == 4 && !(vecX && vecY)))
-                    c.cost = std::max(c.cost, floor);
-        }
-    }
+    return ranked;
+    };
     // Ties (the same estimate to 0.01 us: mirror-image tiles on a square
     // problem) between tiles of at least 64 x 64 go to the one wider along y,
     // whose C runs are longer (measured on MI355X: fp64 64 x 128 x 24 against
@@ -986,11 +1005,29 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         const TileShape &t = tile_shape(dtype, c.tile);
         return t.mt >= 64 && t.nt >= 64 ? t.nt : 0;
     };
-    std::stable_sort(ranked.begin(), ranked.end(), [&](const Candidate &a, const Candidate &b) {
+    auto cheaper = [&](const Candidate &a, const Candidate &b) {
         const long long ka = llround(a.cost * 1e8), kb = llround(b.cost * 1e8);
         if (ka != kb) return ka < kb;
         return wideY(a) > wideY(b);
-    });
+    };
+    // The reference: the cheapest candidate of the model without the cost of
+    // gathers.  That cost moves the choice between kernels; it must not move
+    // what a caller gets, so a candidate that sums in longer chains than the
+    // reference ranks behind the cheapest that does not (the rounding error of
+    // a sum grows as the square root of its chain: fp32 over 3721 positions
+    // 4e-7 of the result's norm in slices, 1.1e-6 in one chain).  The reference
+    // itself is ranked when no other candidate keeps to it.
+    const std::vector<Candidate> plain = candidates(false);
+    const Candidate ref = *std::min_element(plain.begin(), plain.end(), cheaper);
+    maxChain = ref.chain * (1.0 + 1e-9);
+    std::vector<Candidate> ranked = candidates(true);
+    if (std::none_of(ranked.begin(), ranked.end(), keeps)) ranked.push_back(ref);
+    double first = std::numeric_limits<double>::infinity();
+    for (const Candidate &c : ranked)
+        if (keeps(c)) first = std::min(first, c.cost);
+    for (Candidate &c : ranked)
+        if (!keeps(c)) c.cost = std::max(c.cost, 1.01 * first);
+    std::stable_sort(ranked.begin(), ranked.end(), cheaper);
     Candidate pick = ranked[0];
     const char *how = "model";
     auto find = [&](int t, int k) -> const Candidate * {
@@ -1396,15 +1433,19 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
       << ",\"c_order_epilogue\":" << (ts.corder ? "true" : "false")
       << ",\"chosen_by\":\"" << how << "\",\"model_us\":" << pick.cost * 1e6 << "}";
     o << ",\"hooks\":\"" << hk.text << "\"";
+    auto candidate = [&](const Candidate &c) {
+        o << "{\"tile\":" << c.tile << ",\"kind\":\"" << kind_name(c.kind) << "\"";
+        if (c.kind == 2) o << ",\"kslices\":" << c.slices;
+        if (c.kind == 3) o << ",\"tail_workgroups\":" << c.slices;
+        o << ",\"chain\":" << c.chain << ",\"model_us\":" << c.cost * 1e6 << "}";
+    };
     o << ",\"candidates\":[";
     for (size_t i = 0; i < ranked.size(); ++i) {
-        o << (i ? "," : "") << "{\"tile\":" << ranked[i].tile << ",\"kind\":\""
-          << kind_name(ranked[i].kind) << "\"";
-        if (ranked[i].kind == 2) o << ",\"kslices\":" << ranked[i].slices;
-        if (ranked[i].kind == 3) o << ",\"tail_workgroups\":" << ranked[i].slices;
-        o << ",\"model_us\":" << ranked[i].cost * 1e6 << "}";
+        if (i) o << ",";
+        candidate(ranked[i]);
     }
-    o << "]";
+    o << "],\"reference\":";
+    candidate(ref);
     o << ",\"streaming\":" << (streaming ? "true" : "false");
     const bool onDirect = kind == 2 && direct_slices(ts.deff > 0.0f, xmode, ymode);
     o << ",\"kernel\":\"" << (onDirect ? "direct" : kind == 2 ? "macro" : kind_name(kind))

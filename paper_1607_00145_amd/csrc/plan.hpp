@@ -40,6 +40,9 @@ struct Candidate {
     int slices = 1;                         // workgroups per tile (kind 2), tail
                                             // workgroups (kind 3)
     double tMfma = 0, tMem = 0, cost = 0;   // seconds
+    double chain = 0;                       // additions in a row behind an element of C, on
+                                            // average: an MFMA adds four positions at once,
+                                            // a partial tile is one
 };
 
 // A candidate imposed on the analyser, and where the choice came from.
