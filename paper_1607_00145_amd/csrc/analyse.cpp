@@ -244,24 +244,25 @@ static double tail_occupancy(const TileShape &c, double itemB)
 // gathers and LDS reads).
 static double cu_time(int occ, int full, double nb, int tail, double len)
 {
-    std::vector<double> left;
-    int next = 0;
+    // (at most eight wavefronts per SIMD, so at most eight workgroups here)
+    double left[8];
+    int held = 0, next = 0;
+    occ = std::min(occ, 8);
     const int n = full + tail;
     auto work = [&](int i) { return i < full ? nb : len; };
-    while (next < n && (int)left.size() < occ) left.push_back(work(next++));
+    while (next < n && held < occ) left[held++] = work(next++);
     double t = 0.0;
-    while (!left.empty()) {
-        const double w = (double)left.size();
+    while (held > 0) {
         // (a tile that holds one wavefront per SIMD anyway has that rate in
         // its measured efficiency)
-        const double rate = (left.size() >= 2 || occ < 2 ? 1.0 : 0.64) / w;   // per unit, each
-        const double step = *std::min_element(left.begin(), left.end());
+        const double rate = (held >= 2 || occ < 2 ? 1.0 : 0.64) / (double)held;   // per unit, each
+        const double step = *std::min_element(left, left + held);
         t += step / rate;
-        std::vector<double> still;
-        for (double r : left)
-            if (r - step > 1e-9) still.push_back(r - step);
-        left.swap(still);
-        while (next < n && (int)left.size() < occ) left.push_back(work(next++));
+        int still = 0;
+        for (int i = 0; i < held; ++i)
+            if (left[i] - step > 1e-9) left[still++] = left[i] - step;
+        held = still;
+        while (next < n && held < occ) left[held++] = work(next++);
     }
     return t;
 }
@@ -1437,7 +1438,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         o << "{\"tile\":" << c.tile << ",\"kind\":\"" << kind_name(c.kind) << "\"";
         if (c.kind == 2) o << ",\"kslices\":" << c.slices;
         if (c.kind == 3) o << ",\"tail_workgroups\":" << c.slices;
-        o << ",\"chain\":" << c.chain << ",\"model_us\":" << c.cost * 1e6 << "}";
+        o << ",\"model_us\":" << c.cost * 1e6 << "}";
     };
     o << ",\"candidates\":[";
     for (size_t i = 0; i < ranked.size(); ++i) {
@@ -1446,6 +1447,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     }
     o << "],\"reference\":";
     candidate(ref);
+    o << ",\"chain\":" << pick.chain << ",\"reference_chain\":" << ref.chain;
     o << ",\"streaming\":" << (streaming ? "true" : "false");
     const bool onDirect = kind == 2 && direct_slices(ts.deff > 0.0f, xmode, ymode);
     o << ",\"kernel\":\"" << (onDirect ? "direct" : kind == 2 ? "macro" : kind_name(kind))
