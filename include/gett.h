@@ -267,9 +267,10 @@ const char *gett_status_string(gett_status_t status);
  * stream-K tail's whole tiles, workgroups and boxes per workgroup, how C is
  * accessed ("c_access": "vector", 16-byte vectors on the 16-byte grid; "run",
  * vectors at any element address where columns follow one another in C;
- * "element"), the additions in a row behind an element of C ("chain": an
- * MFMA's four positions are one, a partial tile is one) and those of the model's
- * reference, which the plan does not exceed, the partial-tile workspace, grid, the ranked candidates and the flop / byte
+ * "element"), the additions in a row behind an element of C ("chain":
+ * one per contracted position, one per partial tile) and those of the model's
+ * reference, which the plan does not exceed, whether gett_contract_noalloc takes
+ * that reference ("reference_fits"; it then takes the plan too), the partial-tile workspace, grid, the ranked candidates and the flop / byte
  * counts of Eq. 12-14.
  * Returns "" for NULL.
  */

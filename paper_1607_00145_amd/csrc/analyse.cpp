@@ -273,6 +273,16 @@ static double cu_time(int occ, int full, double nb, int tail, double len)
 struct TailShape {
     int64_t full = 0, wgs = 0, len = 0;
 };
+// Chain behind an element of a tile of nb boxes that are dealt in runs of len,
+// as a share of the nb: the pieces' squares over nb squared, averaged over where
+// the runs' ends fall (a sum's squared error grows with the square of each
+// piece's length over the whole's).
+static double tail_chain(int64_t len, int64_t nb)
+{
+    const double l = (double)len, n = (double)nb;
+    if (nb % len == 0 || len % nb == 0) return std::min(1.0, l / n);
+    return l < n ? l / n * (1.0 - l / (3.0 * n)) : 1.0 - n / (3.0 * l);
+}
 static TailShape tail_shape(int64_t T, int64_t nb, int64_t G)
 {
     TailShape s;
@@ -639,9 +649,14 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         cRunY = Iy[0].extent;
         for (size_t i = 1; i < Iy.size() && Iy[i].strC == cRunY; ++i) cRunY *= Iy[i].extent;
     }
-    // The longest chain a candidate may sum in and still rank ahead (below).
+    // The longest chain a candidate may sum in and still rank ahead (below),
+    // and whether its partial tiles have to fit the fixed workspace.
     double maxChain = std::numeric_limits<double>::infinity();
-    auto keeps = [&](const Candidate &c) { return c.chain <= maxChain; };
+    bool mustFit = false;
+    auto keeps = [&](const Candidate &c) { return c.chain <= maxChain && (c.fits || !mustFit); };
+    auto fits = [](double slotBytes, double counters) {
+        return slotBytes <= (double)kFixedSlotBytes && counters <= (double)kFixedCounters;
+    };
     auto better = [&](const Candidate &a, const Candidate &b) {
         if (b.tile < 0 || keeps(a) != keeps(b)) return b.tile < 0 || keeps(a);
         return a.cost < b.cost;
@@ -684,8 +699,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                       std::ceil(wpt / 4.0)
                 : perSimd;
         const double kpad = (double)std::max<int64_t>(b.nsteps, 1) * c.kt;
-        const double oneChain = 0.25 * (double)an.sizeK;
-        const double boxChain = oneChain / (double)std::max<int64_t>(b.nsteps, 1);
+        const double oneChain = (double)an.sizeK;
         const double waveFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * kpad * 2.0;
         // A K split gathers both operands in 16-byte runs whose cache lines
         // return late: a single LDS buffer waits for them (1.4), and so does a
@@ -877,11 +891,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // Tiles that carry the direct-load kernel slice on it (both operands
             // in vectors): its MFMA rate, the slots summed by a second launch
             // (6 us), as many slices as fill the workgroups the CUs hold at
-            // once (two of 128 x 128, one of eight wavefronts) or twice that
-            // many (half the chain), and a workspace within the 64 MiB of
-            // gett_contract_noalloc.  A C of 384 x 376 over 144384: 334 us in
-            // 56 slices, 9.2e-7 of the result's norm; 341 us in 113, 6.7e-7
-            // (64 x 64 tiles of the macro-kernel in 64: 439 us, 8.6e-7).
+            // once (two of 128 x 128, one of eight wavefronts), or two or three
+            // times that many (shorter chains).  A C of 384 x 376 over 144384:
+            // 336 us in 56 slices, 9.1e-7 of the result's norm; 342 us in 113,
+            // 6.5e-7; 364 us in 226, 4.7e-7 (32 x 64 tiles of the macro-kernel
+            // in 64: 431 us, 8.6e-7).
             const bool directSlices = gathers && c.deff > 0.0f && vecX && vecY && !kSplitAhead;
             std::vector<int> counts;
             for (int P = 2; P <= 256; P *= 2) counts.push_back(P);
@@ -889,12 +903,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 counts.clear();
                 const double resident = wpt >= 8 ? 256.0 : 512.0;
                 if (resident / (tx * ty) >= 2.0)
-                    for (int fill = 1; fill <= 2; ++fill)
+                    for (int fill = 1; fill <= 3; ++fill)
                         counts.push_back((int)(fill * resident / (tx * ty)));
             }
             for (int P : counts) {
                 if (b.nsteps / P < 8) continue;
-                if (directSlices && tx * ty * P * tileBytes > 67108864.0) continue;
                 const double wgs = tx * ty * P;
                 const double perSimdP =
                     wpt >= 4 ? cu_time((int)tail_occupancy(c, itemB), (int)std::ceil(wgs / 256.0),
@@ -917,17 +930,14 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 cd.tile = t;
                 cd.kind = 2;
                 cd.slices = P;
-                cd.chain = std::ceil((double)b.nsteps / P) * boxChain + P;
+                // (the sum of the direct-load kernel's slots adds up eight at a time)
+                cd.chain = oneChain / P + (directSlices ? std::min(P, 8) + P / 8 : P);
+                cd.fits = fits(tx * ty * P * tileBytes, tx * ty);
                 cd.tMfma = tM;
                 cd.tMem = tMemP;
                 cd.cost = bound(std::max(tM, tMemP), tChainP) + tPart;
                 if (better(cd, best)) best = cd;
             }
-            // Slots beyond the 64 MiB of gett_contract_noalloc have to pay for
-            // being refused there.
-            if (best.tile >= 0 && dtype == GETT_FLOAT32 && elements &&
-                tx * ty * best.slices * tileBytes > 67108864.0)
-                best.cost *= 1.3;
             // (element-wise gathers wait in turn into one LDS buffer; in fp32
             // measured 1.1-1.2 times the model's time, on 128 x 128 x 32
             // 1.2-1.6)
@@ -982,10 +992,10 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 cd.tile = t;
                 cd.kind = 3;
                 cd.slices = 256 * g;
-                cd.chain = (ts.full * oneChain +
-                            (ntile - ts.full) * (double)std::min(ts.len, (int64_t)b.nsteps) *
-                                boxChain) /
-                           ntile;
+                cd.chain = (ts.full + (ntile - ts.full) * tail_chain(ts.len, b.nsteps)) / ntile *
+                           oneChain;
+                cd.fits = fits(((double)ts.wgs + ntile - (double)ts.full - 1.0) * tileBytes,
+                               ntile - (double)ts.full);
                 cd.tMfma = tM;
                 cd.tMem = tMem;
                 cd.cost = bound(std::max(tM, tMem), tChain) + tPart;
@@ -1015,12 +1025,16 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     // gathers.  That cost moves the choice between kernels; it must not move
     // what a caller gets, so a candidate that sums in longer chains than the
     // reference ranks behind the cheapest that does not (the rounding error of
-    // a sum grows as the square root of its chain: fp32 over 3721 positions
-    // 4e-7 of the result's norm in slices, 1.1e-6 in one chain).  The reference
-    // itself is ranked when no other candidate keeps to it.
+    // a sum grows as the square root of its chain: fp32, measured at contracted
+    // sets of 2160 to 144384 in 1 to 256 slices, 1.79e-8 of the result's norm
+    // times the square root of the positions per slice plus the slices, within
+    // 2%; a tail's 947 against 937), and so does
+    // one that gett_contract_noalloc would refuse where it takes the reference.
+    // The reference itself is ranked when no other candidate keeps to it.
     const std::vector<Candidate> plain = candidates(false);
     const Candidate ref = *std::min_element(plain.begin(), plain.end(), cheaper);
     maxChain = ref.chain * (1.0 + 1e-9);
+    mustFit = ref.fits;
     std::vector<Candidate> ranked = candidates(true);
     if (std::none_of(ranked.begin(), ranked.end(), keeps)) ranked.push_back(ref);
     double first = std::numeric_limits<double>::infinity();
@@ -1447,7 +1461,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     }
     o << "],\"reference\":";
     candidate(ref);
-    o << ",\"chain\":" << pick.chain << ",\"reference_chain\":" << ref.chain;
+    o << ",\"chain\":" << pick.chain << ",\"reference_chain\":" << ref.chain
+      << ",\"reference_fits\":" << (ref.fits ? "true" : "false");
     o << ",\"streaming\":" << (streaming ? "true" : "false");
     const bool onDirect = kind == 2 && direct_slices(ts.deff > 0.0f, xmode, ymode);
     o << ",\"kernel\":\"" << (onDirect ? "direct" : kind == 2 ? "macro" : kind_name(kind))

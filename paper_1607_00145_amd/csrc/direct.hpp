@@ -451,7 +451,8 @@ gett_direct_slice_kernel(const KDesc d, const T *__restrict__ X, const T *__rest
 // C <- alpha * (the sum of a tile's slots, in slice order) + beta * C.  One
 // workgroup per MFMA block position (a, b) of the register tile, so that a
 // tile's slots are read by 16 workgroups at once; eight slots in flight per
-// thread.  Bound by the slots' stream from L2 and the Infinity Cache.
+// thread, which are added up before they join the sum (P / 8 + 8 additions in a
+// row instead of P).  Bound by the slots' stream from L2 and the Infinity Cache.
 template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY>
 __global__ void __launch_bounds__(WM *WN * 64)
 gett_sum_slices_kernel(const KDesc d, const T *__restrict__ W, T *__restrict__ C, const T alpha,
@@ -475,11 +476,13 @@ gett_sum_slices_kernel(const KDesc d, const T *__restrict__ W, T *__restrict__ C
             for (int r = 0; r < 4; ++r)
                 v[q][r] = p0 + q < d.kslices ? slot[(size_t)(p0 + q) * step + r * NTH] : T(0);
 #pragma unroll
-        for (int q = 0; q < kFlight; ++q)
+        for (int q = 1; q < kFlight; ++q)
             if (p0 + q < d.kslices) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) sum[r] = p0 + q == 0 ? v[q][r] : sum[r] + v[q][r];
+                for (int r = 0; r < 4; ++r) v[0][r] += v[q][r];
             }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[r] = p0 == 0 ? v[0][r] : sum[r] + v[0][r];
     }
     int tx, ty;
     tile_of_block(d, u, ntiles, tx, ty);

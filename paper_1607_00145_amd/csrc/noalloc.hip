@@ -4,8 +4,8 @@
 //
 // For callers that cannot allocate device memory (code under HIP graph
 // capture, tight serving loops, harnesses that forbid it).  Each GPU the
-// library runs on holds one copy of the buffer (kScratchTiles bytes of slots
-// and kScratchCounters counters) until the process ends; every call on that
+// library runs on holds one copy of the buffer (kFixedSlotBytes bytes of slots
+// and kFixedCounters counters) until the process ends; every call on that
 // GPU shares it, so calls that overlap in time on one GPU race (serialise
 // them, e.g. on one stream).  A call holds the buffer's lock from the clearing
 // of the counters to its last launch, so that calls from several threads on one
@@ -18,14 +18,10 @@
 
 #include "plan.hpp"
 
-namespace {
-constexpr uint64_t kScratchTiles = 64ull << 20;   // partial-tile slots (bytes)
-constexpr uint64_t kScratchCounters = 1u << 16;   // per-tile counters (int32)
-}  // namespace
-
 // The buffer: slots, then counters.  In host code `scratch` only names the
 // symbol; its device address comes from hipGetSymbolAddress, per device.
-static __device__ __align__(256) unsigned char scratch[kScratchTiles + kScratchCounters * sizeof(int)];
+static __device__ __align__(256) unsigned char
+    scratch[gett::kFixedSlotBytes + gett::kFixedCounters * sizeof(int)];
 
 namespace gett {
 namespace {
@@ -70,13 +66,13 @@ gett_status_t scratch_of_device(Scratch **out)
 gett_status_t static_workspace(hipStream_t stream, uint64_t counters, uint64_t tileBytes,
                                Partials &out)
 {
-    if (counters > kScratchCounters || tileBytes > kScratchTiles) return GETT_ERROR_NOT_SUPPORTED;
+    if (counters > kFixedCounters || tileBytes > kFixedSlotBytes) return GETT_ERROR_NOT_SUPPORTED;
     Scratch *own = nullptr;
     const gett_status_t st = scratch_of_device(&own);
     if (st != GETT_SUCCESS) return st;
     out.hold = std::unique_lock<std::mutex>(own->use);
     unsigned char *base = own->address;
-    int *ctr = reinterpret_cast<int *>(base + kScratchTiles);
+    int *ctr = reinterpret_cast<int *>(base + kFixedSlotBytes);
     if (counters > 0) {
         const unsigned n = (unsigned)counters;
         hipLaunchKernelGGL(clear_counters, dim3((n + 255) / 256), dim3(256), 0, stream, ctr, n);

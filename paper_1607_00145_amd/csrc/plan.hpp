@@ -29,6 +29,11 @@ struct Analysis {
     int64_t maxOffA = 0, maxOffB = 0, maxOffC = 0;   // largest element offsets
 };
 
+// The fixed workspace of gett_contract_noalloc: partial-tile slots (bytes) and
+// per-tile counters (int32).
+constexpr uint64_t kFixedSlotBytes = 64ull << 20;
+constexpr uint64_t kFixedCounters = 1u << 16;
+
 // A kernel candidate: tile shape and kind, with the model's estimate.
 struct Candidate {
     int tile = 0, kind = 0;                 // kind 0: macro-kernel, 1: streaming kernel,
@@ -41,8 +46,10 @@ struct Candidate {
                                             // workgroups (kind 3)
     double tMfma = 0, tMem = 0, cost = 0;   // seconds
     double chain = 0;                       // additions in a row behind an element of C, on
-                                            // average: an MFMA adds four positions at once,
-                                            // a partial tile is one
+                                            // average: one per contracted position, one per
+                                            // partial tile
+    bool fits = true;                       // the partial tiles fit the fixed workspace of
+                                            // gett_contract_noalloc
 };
 
 // A candidate imposed on the analyser, and where the choice came from.
