@@ -97,6 +97,42 @@ def kernels():
     return res
 
 
+# macro-kernels whose time is C's stream: 64 x 128 x 24 and 128 x 64 x 8 fp64,
+# 128 x 128 x 16 fp32 (template integer arguments as in plan_kernel)
+STREAMS = [("d", (64, 128, 24, 2, 2, 2, 2, 3, 1, 1, 1, 0, 0, 0, 0, 0)),
+           ("d", (128, 64, 8, 2, 2, 2, 2, 3, 1, 2, 1, 2, 0, 0, 0, 0)),
+           ("f", (128, 128, 16, 2, 2, 4, 4, 3, 1, 2, 1, 0, 0, 1, 0, 0))]
+
+
+@pytest.mark.parametrize("dtype,args", STREAMS, ids=["64x128x24-f64", "128x64x8-f64",
+                                                      "128x128x16-f32"])
+def test_stores_of_c_do_not_wait_for_each_other(dtype, args, tmp_path):
+    """Between the 16-byte stores of the epilogue no wait for vector memory
+    (which would be one for the stores before it): the loads of C are waited
+    for where they are issued, once per group of rows."""
+    if not os.path.exists(f"{LLVM}/llvm-objdump"):
+        pytest.skip("llvm-objdump not found")
+    name = f"_ZN4gett17gett_macro_kernelI{dtype}" + "".join(f"Li{a}E" for a in args) + "EEv"
+    co = next(c for c in code_objects(g.LIB_PATH) if name.encode() in c)
+    path = str(tmp_path / "k.co")
+    open(path, "wb").write(co)
+    syms = subprocess.run([f"{LLVM}/llvm-readelf", "-s", "-W", path], check=True,
+                          capture_output=True, text=True).stdout
+    full = next(l.split()[-1] for l in syms.splitlines() if name in l and "FUNC" in l)
+    asm = subprocess.run([f"{LLVM}/llvm-objdump", "-d", f"--disassemble-symbols={full}", path],
+                         check=True, capture_output=True, text=True).stdout
+    stores, waits, since = 0, 0, False
+    for line in asm.splitlines():
+        if re.search(r"s_waitcnt.*vmcnt", line):
+            since = True
+        elif re.search(r"global_store_dwordx4 .*\bnt\b", line):
+            waits += since and stores > 0
+            stores, since = stores + 1, False
+    assert stores >= 16, "the epilogue's vector stores"
+    # one group of rows to the next: the wait behind the loads of its C
+    assert waits <= stores // 8, (stores, waits)
+
+
 def plan_kernel(w, kernels):
     """The resources of the kernel the model's plan for workload w launches.
     Template integer arguments of the macro-kernel: MT NT KT WM WN RX RY WPE
