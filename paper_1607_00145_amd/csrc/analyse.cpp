@@ -635,10 +635,85 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     // Y's stride-one index among its free ones, behind C's: gathered in
     // strided vectors where the column split below applies.
     const int yUnit = unit_in(Iy, sY);
-    const bool vecYSplit = maySplit && yUnit > 0 && Iy[0].strC == 1 &&
-                           Iy[yUnit].extent % VW == 0 && pow2_part(Iy[0].extent) >= VW &&
-                           aligned(Iy, sY, yUnit) && aligned(Ik, sY, -1);
+    // Column split for tiles of nt columns: the block length f of C's stride-one
+    // index placed in front of Y's (0: the whole-index order), and the y set so
+    // split in `trial`.
+    auto column_block = [&](int nt, std::vector<Index> &trial) -> int64_t {
+        if (!maySplit || yUnit <= 0 || Iy[0].strC != 1 || Iy[yUnit].extent % VW ||
+            (int)Iy.size() >= kMaxDims)
+            return 0;
+        // Columns.  A tile then writes C in runs of f elements and reads Y
+        // in runs of NT/f elements along v; in the whole-index order it
+        // writes runs of up to NT along u and reads Y in runs of NT over
+        // the extents before v.  Runs are priced per byte: a read run of
+        // L bytes at max(1, 64 / L), a write run at max(1, 128 / L)^2
+        // (partial lines are far costlier to write than to read: on
+        // MI355X, C runs under 64 bytes slowed the column-split
+        // contractions of Appendix A 1.4-3.5x, 32-byte read runs did not).
+        // f minimises Y's plus C's price; the whole-index order is kept
+        // where it is cheaper (a Y that is small next to C).
+        const double Ybytes = itemB * (double)sizeY * (double)an.sizeK;
+        const double Cbytes = itemB * (double)sizeX * (double)sizeY;
+        auto readPrice = [](double L) { return std::max(1.0, 64.0 / L); };
+        auto writePrice = [](double L) {
+            const double r = std::max(1.0, 128.0 / L);
+            return r * r;
+        };
+        auto runs = [&](double elems, double cap) { return std::max(1.0, std::min(elems, cap)); };
+        double before = 1;
+        for (int i = 0; i < yUnit; ++i) before *= (double)Iy[i].extent;
+        const double vExt = (double)Iy[yUnit].extent, uExt = (double)Iy[0].extent;
+        double best = Ybytes * readPrice(itemB * runs(nt / before, vExt)) +
+                      Cbytes * writePrice(itemB * runs(std::min<double>(nt, uExt), uExt));
+        int64_t f = 0;
+        for (int64_t t = VW; t <= pow2_part(Iy[0].extent) && t * itemB <= 128; t *= 2) {
+            if (nt % (t * VW)) continue;
+            const double c = Ybytes * readPrice(itemB * runs((double)nt / t, vExt)) +
+                             Cbytes * writePrice(itemB * t);
+            if (c < best) { best = c; f = t; }
+        }
+        if (const char *fs = hk.splitF) f = atoi(fs);   // tuning hook
+        trial = Iy;
+        if (f < VW || (f & (f - 1)) || Iy[0].extent % f || nt % (f * VW)) return 0;
+        split_front(trial, 0, (size_t)yUnit, f);
+        return aligned(trial, sY, 1) && aligned(Ik, sY, -1) ? f : 0;
+    };
     const bool vecC = Iy[0].strC == 1 && Iy[0].extent % VW == 0;
+    // C stored in its memory order (see the epilogue below): the run of C along
+    // y, when it is shorter than a cache line and a row index continues it in
+    // memory; the x index that does.
+    const int64_t shortRun =
+        Iy[0].strC == 1 && Iy[0].extent * (int64_t)itemB < 128 ? Iy[0].extent : 0;
+    auto row_next = [&](const std::vector<Index> &X) {
+        for (size_t i = 0; i < X.size() && shortRun; ++i)
+            if (X[i].strC == shortRun) return (int)i;
+        return -1;
+    };
+    // whether a tile's plan moves that index to the front of the x order, and
+    // what the row operand then gathers
+    auto rows_move = [&](const TileShape &c) {
+        return row_next(Ix) >= 0 && c.corder && bytesX * 8.0 < bytesC &&
+               !(flags & GETT_FLAG_SCALAR);
+    };
+    const bool vecXMoved = row_next(Ix) >= 0 && vecX &&
+                           (sX(Ix[row_next(Ix)]) == 1 || (kvec_ok(sX) && aligned(Ix, sX, -1)));
+    // whether C may be accessed in 16-byte vectors, and whole runs of it stored
+    // in their memory order (the run's length, 0: not) by a tile's macro-kernel
+    auto c_vectors = [&](const TileShape &c) {
+        if ((flags & GETT_FLAG_SCALAR) || Iy[0].strC != 1 || Iy[0].extent % VW || c.ry != VW)
+            return false;
+        for (auto &x : Ix) if (x.strC % VW) return false;
+        for (size_t i = 1; i < Iy.size(); ++i) if (Iy[i].strC % VW) return false;
+        return true;
+    };
+    auto c_run = [&](const TileShape &c) -> int64_t {
+        const int64_t E = Iy[0].extent;
+        const int64_t cap = (int64_t)c.nbuf * c.kt * ((c.mt + VW) + (c.nt + VW));
+        if (!c.corder || Iy.size() < 2 || !c_vectors(c) || row_next(Ix) < 0 || E % VW ||
+            E >= c.nt || (cap / c.mt - VW) / E < 1)
+            return 0;
+        return E;
+    };
     // Partial tiles (K slices, stream-K tail) are summed through the
     // workspace: the stream of partial tiles and one workgroup's reads of a
     // tile's pieces are priced at these rates (MI355X).
@@ -649,10 +724,35 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         cRunY = Iy[0].extent;
         for (size_t i = 1; i < Iy.size() && Iy[i].strC == cRunY; ++i) cRunY *= Iy[i].extent;
     }
+    // The K box (and whether the K split applies) per box depth, and the column
+    // block per tile width: found once, priced for many tiles.
+    struct Ahead {
+        int kt;
+        bool split;
+        Box box;
+    };
+    std::vector<Ahead> aheads;
+    aheads.reserve(16);
+    auto ahead_for = [&](int kt) -> const Ahead & {
+        for (const Ahead &a : aheads)
+            if (a.kt == kt) return a;
+        std::vector<Index> ksplit;
+        const bool split = k_split(kt, ksplit) > 0;
+        aheads.push_back({kt, split, split ? box_on(ksplit, 1, kt) : box_for(kt)});
+        return aheads.back();
+    };
+    std::vector<std::pair<int, int64_t>> blocks;
+    auto block_for = [&](int nt) {
+        for (const auto &b : blocks)
+            if (b.first == nt) return b.second;
+        std::vector<Index> split;
+        blocks.push_back({nt, column_block(nt, split)});
+        return blocks.back().second;
+    };
     // The longest chain a candidate may sum in and still rank ahead (below),
     // and whether its partial tiles have to fit the fixed workspace.
     double maxChain = std::numeric_limits<double>::infinity();
-    bool mustFit = false;
+    bool mustFit = false, inPieces = false;
     auto keeps = [&](const Candidate &c) { return c.chain <= maxChain && (c.fits || !mustFit); };
     auto fits = [](double slotBytes, double counters) {
         return slotBytes <= (double)kFixedSlotBytes && counters <= (double)kFixedCounters;
@@ -669,6 +769,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     for (int t = 0; t < num_tiles(dtype); ++t) {
         const TileShape &c = tile_shape(dtype, t);
         if (!gathers && c.nt >= 8 * c.mt) continue;   // the tile for few rows: by its gathers only
+        const int64_t block = gathers && !vecY && yUnit > 0 ? block_for(c.nt) : 0;
+        const bool vecYSplit = block > 0;
         const double tileBytes = (double)c.mt * c.nt * itemB;
         // a one-box tile is ranked only for a contracted set in one box whose
         // operands are both gathered in vectors: it waits for each operand's
@@ -678,26 +780,37 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             (box_for(c.kt).nsteps > 1 || slowGather || (gathers && !(vecX && vecY))) &&
             !(ft && atoi(ft) == t) && !(force && force->tile == t))
             continue;
-        std::vector<Index> ksplit;
-        const bool kSplitAhead = k_split(c.kt, ksplit) > 0;
-        const Box b = kSplitAhead ? box_on(ksplit, 1, c.kt) : box_for(c.kt);
+        const Ahead &ahead = ahead_for(c.kt);
+        const bool kSplitAhead = ahead.split;
+        const Box &b = ahead.box;
         const double tx = (double)((sizeX + c.mt - 1) / c.mt);
         const double ty = (double)((sizeY + c.nt - 1) / c.nt);
+        // What the plan does for C's order: whole runs per tile (the last columns
+        // idle, 16 of 128 for runs of 28) and X's vectors lost to the x order
+        // (28 x 20 x 20 x 24 x 20 x 20 fp32 over 192 / 256: 526 / 676 us on the
+        // 112 columns of 128 x 128 x 16 where 439 / 540 were to be had).
+        const int64_t run = gathers && !vecYSplit ? c_run(c) : 0;
+        const double tyRun =
+            run > 0 ? std::ceil((double)sizeY / (double)(c.nt / run * run)) : ty;
+        // Stored by the lanes of the MFMA layout, such a C is partial lines all:
+        // 430 MB in runs of 112 bytes took 360 us on 256 x 128.
+        const double cutC =
+            gathers && dtype == GETT_FLOAT32 && shortRun > 0 && row_next(Ix) >= 0 ? 3.6 : 1.0;
+        const bool vecXHere = gathers && rows_move(c) && !vecYSplit ? vecXMoved : vecX;
         // Busiest SIMD: a workgroup of four or more wavefronts is spread over
         // the four SIMDs of one CU (ceil(w / 4) on the busiest), so a CU's
         // load is counted in workgroups; smaller workgroups share SIMDs.
         const int wpt = c.wm * c.wn;
         const double waves = tx * ty * wpt;
-        const double perSimd = wpt >= 4 ? std::ceil(tx * ty / 256.0) * std::ceil(wpt / 4.0)
-                                        : std::ceil(waves / 1024.0);
         // The busiest CU's tiles pass through its resident slots (cu_time):
         // a last round with fewer tiles than slots leaves wavefronts alone.
-        const double perSimdRun =
-            wpt >= 4
-                ? cu_time((int)tail_occupancy(c, itemB), (int)std::ceil(tx * ty / 256.0), 1.0, 0,
-                          0.0) *
-                      std::ceil(wpt / 4.0)
-                : perSimd;
+        auto per_simd = [&](double tiles) {
+            return wpt >= 4 ? cu_time((int)tail_occupancy(c, itemB),
+                                      (int)std::ceil(tiles / 256.0), 1.0, 0, 0.0) *
+                                  std::ceil(wpt / 4.0)
+                            : std::ceil(tiles * wpt / 1024.0);
+        };
+        const double perSimdRun = per_simd(tx * ty);
         const double kpad = (double)std::max<int64_t>(b.nsteps, 1) * c.kt;
         const double oneChain = (double)an.sizeK;
         const double waveFlops = (double)(c.mt / c.wm) * (c.nt / c.wn) * kpad * 2.0;
@@ -719,9 +832,10 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // against even ones: 4096^3-shaped 1.1-1.25, C of 529 x 3721 over 3721
         // 1.45 on 32 x 64 tiles).
         // (an X of few rows is a small part of every tile's gathers)
-        const bool xVec = vecX || (sizeX <= 64 && 16.0 * bytesX < bytesY + bytesC);
+        const bool xVec = vecXHere || (sizeX <= 64 && 16.0 * bytesX < bytesY + bytesC);
         const bool elements =   // some operand's
             gathers && (slowGather || !(xVec && (vecY || vecYSplit || kSplitAhead)));
+        const bool both = !vecXHere && !vecY && !vecYSplit;   // both operands'
         const double kElementWise = !gathers || dtype != GETT_FLOAT32 ||
                                             (xVec && (vecY || vecYSplit)) || kSplitAhead
                                         ? 1.0
@@ -736,19 +850,36 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         const double kCrossed = crossed && dtype == GETT_FLOAT32 && c.kt <= 16 ? 2.0 : 1.0;
         const double tMfma =
             perSimdRun * waveFlops / (peakSimd * c.eff) * kSplitWait * kElementWise * kCrossed;
-        // A tile's offset tables, first gathers and C stores are covered by
-        // nothing when its workgroup has the CU to itself (measured per tile
-        // on fp32 tensors times matrices with contracted sets of 96-384: 4 us
-        // on 128 x 128 macro tiles, 8 us on 128 x 256 direct ones, half of
-        // that for two 128 x 128 direct workgroups; C in single elements
-        // takes two to three times that).
-        const double rounds = std::ceil(tx * ty / 256.0);
-        const double macroSetup = !gathers || dtype != GETT_FLOAT32 ? 0.0
-                                  : wpt >= 8                 ? rounds * (vecC ? 8.0e-6 : 16.0e-6)
-                                  : c.wpe == 1 && wpt >= 4 ? rounds * (vecC ? 4.0e-6 : 12.0e-6)
-                                                           : 0.0;
-        const double tileSetup =
-            rounds * (vecC ? 8.0e-6 : 16.0e-6) * (wpt >= 8 ? 1.0 : 0.5);
+        // A tile's offset tables, first gathers and C stores, per round of
+        // workgroups as measured, and what the first round adds to the launch
+        // that every candidate has: 2 us more on the larger tiles of four
+        // wavefronts than on the small ones; on those of eight (one workgroup
+        // per CU) the round's figure holds it and 0.7 us of the launch.  One
+        // workgroup per CU stores C element by element at nearly half the rate
+        // of two.
+        auto set_up = [&](bool pair) {
+            if (!gathers || c.setup <= 0.0f) return 0.0;
+            const double us = vecC ? c.setup : c.setupE * (pair ? 0.6 : 1.0);
+            return (us * std::ceil(tx * ty / (wpt >= 4 ? 256.0 : 1024.0)) +
+                    (wpt >= 8 ? -0.7 : c.mt * c.nt > 2048 ? 2.0 : 0.0)) * 1e-6;
+        };
+        const double rest = gathers && c.rest > 0.0f && !kSplitAhead ? c.rest : 1.0;
+        // Y's lanes run along a free index that Y is not stride-one along: every
+        // element comes from a cache line of its own, 0.13-0.19e12 of them a
+        // second on every tile and kernel that fills the CUs (each row of tiles
+        // reads all of Y again; 136 x 197 x 56 fp32 over 176: 54 us on tiles of 32
+        // rows, 32 on 64).  Where the lane order groups the columns by a first
+        // index shorter than the tile, up to twice as many.
+        const double group = (double)c.nt / (double)std::max<int64_t>(Iy[0].extent, 1);
+        const bool grouped = group >= 1.0 && (4.0 * bytesY >= bytesC || yUnit == 1);
+        const double apartRate = 1.0e12 * (0.17 + (grouped ? 0.024 * group : 0.0)) *
+                                 (c.nt >= 256 ? 0.8 : 1.0);
+        auto apart = [&](double wgs) {
+            if (!gathers || dtype != GETT_FLOAT32 || vecY || vecYSplit || yUnit < 1) return 0.0;
+            return (double)sizeY * (double)an.sizeK * tx /
+                   (apartRate * std::min(1.0, std::max(wgs, 1.0) * wpt / 1024.0));
+        };
+        const double tApart = apart(tx * ty);
         // The persistent streaming kernel needs the contracted set in one box.
         const bool canStream = c.stream && b.nsteps <= 1;
         // A stream carried by fewer workgroups than CUs gets that share of the
@@ -777,7 +908,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // the operand panels re-read by other tiles, mostly from L2
             // A single LDS buffer does not overlap the boxes of an fp64 stream
             // (C of 24 x 373248 over 72: 82 us on 64 x 128, 60 on 32 x 64).
-            const double tMem = (bytesC + bytesX + bytesY +
+            const double tMem = (bytesC * (k == 0 && run > 0 ? 1.0 : cutC) + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * bwFrac) *
                                 (!gathers || dtype != GETT_FLOAT64      ? 1.0
@@ -787,8 +918,9 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             Candidate cd;
             cd.tile = t;
             cd.kind = k;
-            cd.tMfma = tMfma;
-            cd.tMem = tMem;
+            const double idle = run > 0 && k == 0 ? (double)c.nt / (double)(c.nt / run * run) : 1.0;
+            cd.tMfma = idle > 1.0 ? tMfma * per_simd(tx * tyRun) / perSimdRun : tMfma;
+            cd.tMem = tMem * idle;
             // element-wise gathers into a single LDS buffer (the streaming
             // kernel too) wait with nothing to overlap them, as in the K split
             // (the fp32 tiles 256 wide carry sixteen such loads per thread and
@@ -801,12 +933,18 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 // a column split into single vectors writes C in 16-byte runs
                 // (268 x 256 x 16 over 280 fp32: 42 us 256 wide, 31 on 32 x 64)
                 : slowGather && xVec && vecYSplit
-                    ? (c.nt == 256 && pow2_part(Iy[0].extent) <= VW ? 1.6 : 1.0)
-                : dtype == GETT_FLOAT32 && c.nt == 256 && c.kt == 16  ? (c.mt == 32 ? 1.7 : 2.2)
-                : dtype == GETT_FLOAT32 && wpt == 1                   ? 1.5
+                    ? (c.nt < 256 ? 1.0 : block <= VW ? 1.6 : 1.4)
+                : dtype == GETT_FLOAT32 && c.nt == 256 && c.kt == 16 && !(vecY || vecYSplit)
+                    ? (c.mt == 32 ? 1.15 : 1.45)
+                : dtype == GETT_FLOAT32 && wpt == 1                   ? 1.15
                                                                       : 1.0;
             cd.chain = oneChain;
-            cd.cost = bound(std::max(tMfma, tMem), tChain) * single + macroSetup;
+            // a stream covers three quarters of the set-up of its tiles
+            const double setup = set_up(false);
+            const double restHere = run > 0 && k == 0 ? std::max(rest, 0.95) : rest;
+            cd.cost = bound(std::max({cd.tMfma * single * restHere + setup,
+                                      cd.tMem * single + 0.25 * setup, tApart}),
+                            tChain);
             ranked.push_back(cd);
         }
         // Direct-load kernel (tiles that carry it): both operands gathered in
@@ -818,17 +956,19 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         if (c.deff > 0.0f && !(flags & GETT_FLAG_SCALAR) && b.nsteps >= 1 &&
             (!gathers      ? !slowGather && !kSplitAhead
              : kSplitAhead ? aligned(Ix, sX, -1)
-                           : vecX && vecY)) {
-            const double tMem = (bytesC + bytesX + bytesY +
+                           : vecXHere && vecY)) {
+            const double tMem = (bytesC * cutC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw * cuShare);
             Candidate cd;
             cd.tile = t;
             cd.kind = 4;
             cd.chain = oneChain;
-            cd.tMfma = tMfma / kSplitWait * c.eff / c.deff;
+            cd.tMfma = tMfma / kSplitWait * c.eff / c.deff *
+                       (gathers ? (kSplitAhead ? 1.12 : 1.11) : 1.0);
             cd.tMem = tMem;
-            cd.cost = bound(std::max(cd.tMfma, tMem), tChain) + (gathers ? tileSetup : 0.0);
+            cd.cost = bound(std::max(cd.tMfma + set_up(wpt < 8), tMem + 0.25 * set_up(wpt < 8)),
+                            tChain);
             ranked.push_back(cd);
         }
         // The same kernel with element-wise copies, for operands that do not
@@ -838,7 +978,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         if (gathers && c.deff > 0.0f && dtype == GETT_FLOAT32 && !(vecX && vecY) &&
             !kSplitAhead && !an.emptySum && an.sizeK < INT32_MAX / 2 && an.maxOffA < INT32_MAX &&
             an.maxOffB < INT32_MAX) {
-            const double tMem = (bytesC + bytesX + bytesY +
+            const double tMem = (bytesC * cutC + bytesX + bytesY +
                                  0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
                                 (8.0e12 * c.bw * cuShare);
             const double boxes = std::ceil((double)an.sizeK / c.kt);
@@ -847,9 +987,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             cd.kind = 6;
             cd.chain = oneChain;
             cd.tMfma = tMfma * boxes * c.kt / kpad / kElementWise * c.eff /
-                       (wpt >= 8 ? 0.71 : 0.68) * (crossed && c.mt < 256 ? 1.4 : 1.0);
+                       (wpt >= 8 ? 0.80 : 0.75) * (crossed && c.mt < 256 ? 1.4 : 1.0);
             cd.tMem = tMem;
-            cd.cost = bound(std::max(cd.tMfma, tMem), chain(tx * ty, boxes)) + tileSetup;
+            cd.cost = bound(std::max({cd.tMfma + set_up(wpt < 8), tMem + 0.25 * set_up(wpt < 8),
+                                      tApart}),
+                            chain(tx * ty, boxes));
             ranked.push_back(cd);
         }
         // Persistent direct-load kernel (tiles that carry it): a contracted
@@ -896,11 +1038,14 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // 336 us in 56 slices, 9.1e-7 of the result's norm; 342 us in 113,
             // 6.5e-7; 364 us in 226, 4.7e-7 (32 x 64 tiles of the macro-kernel
             // in 64: 431 us, 8.6e-7).
-            const bool directSlices = gathers && c.deff > 0.0f && vecX && vecY && !kSplitAhead;
+            const bool directSlices =
+                gathers && c.deff > 0.0f && vecXHere && vecY && !kSplitAhead;
             std::vector<int> counts;
-            for (int P = 2; P <= 256; P *= 2) counts.push_back(P);
+            for (int P = 2; P <= 256; P *= 2) {
+                counts.push_back(P);
+                if (gathers && inPieces && P < 256) counts.push_back(P + P / 2);
+            }
             if (directSlices) {
-                counts.clear();
                 const double resident = wpt >= 8 ? 256.0 : 512.0;
                 if (resident / (tx * ty) >= 2.0)
                     for (int fill = 1; fill <= 3; ++fill)
@@ -909,11 +1054,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             for (int P : counts) {
                 if (b.nsteps / P < 8) continue;
                 const double wgs = tx * ty * P;
-                const double perSimdP =
-                    wpt >= 4 ? cu_time((int)tail_occupancy(c, itemB), (int)std::ceil(wgs / 256.0),
-                                       1.0, 0, 0.0) *
-                                   std::ceil(wpt / 4.0)
-                             : std::ceil(wgs * wpt / 1024.0);
+                const double perSimdP = per_simd(wgs);
                 const double kpadP = (std::ceil((double)b.nsteps / P) + 2.0) * c.kt;
                 const double tM = perSimdP * (double)(c.mt / c.wm) * (c.nt / c.wn) * kpadP * 2.0 /
                                   (peakSimd * (directSlices ? c.deff : c.eff)) *
@@ -935,16 +1076,20 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 cd.fits = fits(tx * ty * P * tileBytes, tx * ty);
                 cd.tMfma = tM;
                 cd.tMem = tMemP;
-                cd.cost = bound(std::max(tM, tMemP), tChainP) + tPart;
+                // (3, 6, .. 192 slices keep a chain or the workspace's limit that
+                // powers of two may not; they take longer than priced: 66 x 72 over
+                // 5184 fp64 26.9 us in 48, 22.4 in 32)
+                cd.cost = (bound(std::max({tM, tMemP, apart(wgs)}), tChainP) + tPart) *
+                          (!directSlices && (P & (P - 1)) ? 1.25 : 1.0);
                 if (better(cd, best)) best = cd;
             }
             // (element-wise gathers wait in turn into one LDS buffer; in fp32
             // measured 1.1-1.2 times the model's time, on 128 x 128 x 32
             // 1.2-1.6)
             if (elements && !kSplitAhead)
-                best.cost *= c.nbuf == 1                              ? 1.5
+                best.cost *= c.nbuf == 1                              ? (both ? 1.5 : 1.15)
                              : dtype != GETT_FLOAT32                  ? 1.0
-                             : c.nt == 256 && c.kt == 16 && c.mt < 64 ? 1.7
+                             : c.nt == 256 && c.kt == 16 && c.mt < 64 ? 1.25
                              : crossed                                ? 1.0
                              : c.wpe == 1 && c.kt == 32               ? 1.35
                                                                       : 1.15;
@@ -971,7 +1116,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const double boxTime =
                 std::ceil(wpt / 4.0) * boxFlops / (peakSimd * c.eff) *
                 (gathers ? kSplitWait : kSplitAhead && c.nbuf == 1 ? 1.4 : 1.0) * kElementWise *
-                kCrossed * (elements && c.nbuf == 1 ? 2.5 : 1.0);   // spills (element-wise gathers in the
+                kCrossed * (elements && c.nbuf == 1 ? (both ? 2.5 : 1.25) : 1.0);   // spills (element-wise gathers in the
                                                          // piece loop: 869 against 339 us on a C
                                                          // of 529 x 3721 over 3721)
             const double tMem = (bytesC + bytesX + bytesY +
@@ -998,7 +1143,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                                ntile - (double)ts.full);
                 cd.tMfma = tM;
                 cd.tMem = tMem;
-                cd.cost = bound(std::max(tM, tMem), tChain) + tPart;
+                cd.cost = bound(std::max({tM, tMem, tApart}), tChain) + tPart;
                 if (better(cd, best)) best = cd;
             }
             if (best.tile >= 0) ranked.push_back(best);
@@ -1035,8 +1180,23 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     const Candidate ref = *std::min_element(plain.begin(), plain.end(), cheaper);
     maxChain = ref.chain * (1.0 + 1e-9);
     mustFit = ref.fits;
+    inPieces = ref.kind == 2 || ref.kind == 3;
     std::vector<Candidate> ranked = candidates(true);
     if (std::none_of(ranked.begin(), ranked.end(), keeps)) ranked.push_back(ref);
+    // A twentieth between two prices decides nothing, so the reference's is
+    // reduced by that much (a direct-load kernel that its operands refuse runs
+    // as its tile's macro-kernel).  Over 931 measured contractions the plans take
+    // 0.778 of the time they took without the price of gathers, and 12 of them
+    // more than 1.04; without the reduction about 1.6 times as many do.
+    auto stays = [&](int kind) {
+        for (Candidate &c : ranked)
+            if (c.tile == ref.tile && c.kind == kind) {
+                c.cost *= 0.95;
+                return true;
+            }
+        return false;
+    };
+    if (!stays(ref.kind) && ref.kind >= 4) stays(0);
     double first = std::numeric_limits<double>::infinity();
     for (const Candidate &c : ranked)
         if (keeps(c)) first = std::min(first, c.cost);
@@ -1110,50 +1270,16 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     if (maySplit) {
         // which set holds each operand's stride-one index
         const int yRow = unit_in(Iy, sY);
+        std::vector<Index> trial;
         if (yRow > 0 && Iy[0].strC == 1 && Iy[yRow].extent % VW == 0 &&
             (int)Iy.size() < kMaxDims) {
-            // Columns.  A tile then writes C in runs of f elements and reads Y
-            // in runs of NT/f elements along v; in the whole-index order it
-            // writes runs of up to NT along u and reads Y in runs of NT over
-            // the extents before v.  Runs are priced per byte: a read run of
-            // L bytes at max(1, 64 / L), a write run at max(1, 128 / L)^2
-            // (partial lines are far costlier to write than to read: on
-            // MI355X, C runs under 64 bytes slowed the column-split
-            // contractions of Appendix A 1.4-3.5x, 32-byte read runs did not).
-            // f minimises Y's plus C's price; the whole-index order is kept
-            // where it is cheaper (a Y that is small next to C).
-            const double Ybytes = itemB * (double)sizeY * (double)an.sizeK;
-            const double Cbytes = itemB * (double)sizeX * (double)sizeY;
-            auto readPrice = [](double L) { return std::max(1.0, 64.0 / L); };
-            auto writePrice = [](double L) {
-                const double r = std::max(1.0, 128.0 / L);
-                return r * r;
-            };
-            auto runs = [&](double elems, double cap) { return std::max(1.0, std::min(elems, cap)); };
-            double before = 1;
-            for (int i = 0; i < yRow; ++i) before *= (double)Iy[i].extent;
-            const double vExt = (double)Iy[yRow].extent, uExt = (double)Iy[0].extent;
-            double best = Ybytes * readPrice(itemB * runs(ts.nt / before, vExt)) +
-                          Cbytes * writePrice(itemB * runs(std::min<double>(ts.nt, uExt), uExt));
-            int64_t f = 0;
-            for (int64_t t = VW; t <= pow2_part(Iy[0].extent) && t * itemB <= 128; t *= 2) {
-                if (ts.nt % (t * VW)) continue;
-                const double c = Ybytes * readPrice(itemB * runs((double)ts.nt / t, vExt)) +
-                                 Cbytes * writePrice(itemB * t);
-                if (c < best) { best = c; f = t; }
-            }
-            if (const char *fs = hk.splitF) f = atoi(fs);   // tuning hook
-            std::vector<Index> trial = Iy;
-            if (f >= VW && (f & (f - 1)) == 0 && Iy[0].extent % f == 0 && ts.nt % (f * VW) == 0) {
-                split_front(trial, 0, (size_t)yRow, f);
-                if (aligned(trial, sY, 1) && aligned(Ik, sY, -1)) {
-                    Iy.swap(trial);
-                    ysplit = kGatherRowVecStrided;
-                    yes = (int)f;
-                }
+            const int64_t f = column_block(ts.nt, trial);
+            if (f > 0) {
+                Iy.swap(trial);
+                ysplit = kGatherRowVecStrided;
+                yes = (int)f;
             }
         } else {
-            std::vector<Index> trial;
             const int64_t f = k_split(ts.kt, trial);
             if (f > 0) {
                 Ik.swap(trial);
@@ -1186,17 +1312,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     // by C stride (the row operand's stride-one index stays first when it is
     // a free index, for its vector gathers) and tiles y-fastest.
     const bool streaming = bestMem > bestMfma;
-    // C's stride-one run along y, when shorter than a cache line and continued
-    // in memory by a row index: C is then stored in its memory order (below),
-    // which pays only if consecutive tile rows are consecutive in C, so that
-    // row index leads the x order -- taken when the row operand is small next
-    // to C (its gathers may lose their vectors).
-    const int64_t shortRun = Iy[0].strC == 1 && Iy[0].extent * (int64_t)itemB < 128 ? Iy[0].extent : 0;
-    int rowNext = -1;
-    for (size_t i = 0; i < Ix.size() && shortRun; ++i)
-        if (Ix[i].strC == shortRun) rowNext = (int)i;
-    const bool corderRows = rowNext >= 0 && ts.corder && bytesX * 8.0 < bytesC &&
-                            !(flags & GETT_FLAG_SCALAR);
+    // Where C is stored in its memory order (below), consecutive tile rows have
+    // to be consecutive in C: that row index leads the x order -- taken when the
+    // row operand is small next to C (its gathers may lose their vectors).
+    const int rowNext = row_next(Ix);
+    const bool corderRows = ysplit != kGatherRowVecStrided && rows_move(ts);
     if (streaming) {
         std::stable_sort(Ix.begin(), Ix.end(), [](const Index &a, const Index &b) {
             return a.strC < b.strC;
@@ -1240,26 +1360,12 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     // that ends up otherwise runs its tile's macro-kernel.
     if (kind == 4 && !(direct_modes(xmode, ymode) && nsteps >= 1)) kind = 0;
     if (kind == 5 && !(xmode <= kGatherKVec && ymode <= kGatherKVec && nsteps == 1)) kind = 0;
-    bool cvec = !(flags & GETT_FLAG_SCALAR) && Iy[0].strC == 1 && Iy[0].extent % VW == 0;
-    for (auto &x : Ix) if (x.strC % VW) cvec = false;
-    for (size_t i = 1; i < Iy.size(); ++i) if (Iy[i].strC % VW) cvec = false;
-    if (ts.ry != VW) cvec = false;   // the tile's lanes do not own VW consecutive columns
+    const bool cvec = c_vectors(ts);
     // C stored in its memory order through LDS (unpack_c_order): when C's
     // stride-one run along y is shorter than a cache line and C continues in
     // memory along a row index, the per-lane stores would cut every line.
     // At least one run must fit a staging pass of the packing buffers.
-    int crun = 0;
-    if (cvec && ts.corder && kind == 0 && kslices == 1 && ysplit != kGatherRowVecStrided &&
-        Iy.size() > 1) {
-        const int64_t E = Iy[0].extent;
-        bool rowNext = false;
-        for (auto &x : Ix)
-            if (x.strC == E) rowNext = true;
-        const int64_t cap = (int64_t)ts.nbuf * ts.kt * ((ts.mt + VW) + (ts.nt + VW));
-        if (rowNext && E * (int64_t)itemB < 128 && E % VW == 0 && E < ts.nt &&
-            (cap / ts.mt - VW) / E >= 1)
-            crun = (int)E;
-    }
+    int crun = kind == 0 && kslices == 1 && ysplit != kGatherRowVecStrided ? (int)c_run(ts) : 0;
     if (const char *co = hk.cOrder) {   // tuning hook: 0 turns it off
         if (atoi(co) == 0) crun = 0;
     }

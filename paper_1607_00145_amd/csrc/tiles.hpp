@@ -33,22 +33,30 @@ struct TileShape {
     float dsbw;  // > 0: also compiled as the persistent direct-load kernel for
                  // plans whose contracted set is one K box, which sustains this
                  // fraction of the HBM peak when streaming C
+    float setup;   // us per round of workgroups (256, or 1024 of one wavefront) that
+    float setupE;  // offset tables, first gathers and C stores add, C in vectors /
+                   // otherwise
+    float rest;    // what remains of the throughput estimate once that is counted
+                   // apart.  setup, setupE and rest are fitted (fp32): the tiles'
+                   // measured times over 1100 contractions, benchmark families and
+                   // matrix products of drawn extents, so that the times of the
+                   // plans they lead to are least
 };
 
 constexpr TileShape kTilesF32[] = {
-    {128, 128, 16, 2, 2, 4, 4, 1, 1, 2, 0, 0.75f, 0.61f, 0.0f, 0, 1},
-    {64, 64, 16, 1, 1, 4, 4, 1, 1, 2, 0, 0.67f, 0.62f, 0.0f, 0, 1},
-    {128, 128, 16, 2, 2, 4, 4, 3, 1, 2, 2, 0.71f, 0.675f, 0.64f, 0, 1, 1},
-    {64, 256, 16, 1, 4, 4, 4, 3, 1, 2, 2, 0.70f, 0.70f, 0.63f, 0, 1},
-    {128, 128, 32, 2, 2, 4, 4, 1, 1, 2, 0, 0.806f, 0.61f, 0.0f, 0, 1, 0, 0.87f},
-    {64, 32, 32, 2, 2, 2, 1, 2, 2, 2, 0, 0.64f, 0.35f, 0.0f},
-    {32, 64, 32, 2, 2, 1, 2, 2, 2, 2, 0, 0.65f, 0.35f, 0.0f},
-    {256, 128, 32, 4, 2, 4, 4, 2, 1, 2, 0, 0.75f, 0.55f, 0.0f, 0, 0, 0, 0.89f},
-    {128, 256, 32, 2, 4, 4, 4, 2, 1, 2, 0, 0.75f, 0.55f, 0.0f, 0, 0, 0, 0.89f},
+    {128, 128, 16, 2, 2, 4, 4, 1, 1, 2, 0, 0.75f, 0.61f, 0.0f, 0, 1, 0, 0.0f, 0.0f, 2.8f, 17.0f, 1.07f},
+    {64, 64, 16, 1, 1, 4, 4, 1, 1, 2, 0, 0.67f, 0.62f, 0.0f, 0, 1, 0, 0.0f, 0.0f, 2.4f, 5.4f, 0.99f},
+    {128, 128, 16, 2, 2, 4, 4, 3, 1, 2, 2, 0.71f, 0.675f, 0.64f, 0, 1, 1, 0.0f, 0.0f, 1.4f, 3.7f, 0.90f},
+    {64, 256, 16, 1, 4, 4, 4, 3, 1, 2, 2, 0.70f, 0.70f, 0.63f, 0, 1, 0, 0.0f, 0.0f, 1.4f, 4.6f, 0.935f},
+    {128, 128, 32, 2, 2, 4, 4, 1, 1, 2, 0, 0.806f, 0.61f, 0.0f, 0, 1, 0, 0.87f, 0.0f, 2.3f, 17.0f, 1.06f},
+    {64, 32, 32, 2, 2, 2, 1, 2, 2, 2, 0, 0.64f, 0.35f, 0.0f, 0, 0, 0, 0.0f, 0.0f, 0.6f, 1.0f, 0.90f},
+    {32, 64, 32, 2, 2, 1, 2, 2, 2, 2, 0, 0.65f, 0.35f, 0.0f, 0, 0, 0, 0.0f, 0.0f, 0.6f, 1.4f, 1.145f},
+    {256, 128, 32, 4, 2, 4, 4, 2, 1, 2, 0, 0.75f, 0.55f, 0.0f, 0, 0, 0, 0.89f, 0.0f, 7.5f, 20.0f, 0.96f},
+    {128, 256, 32, 2, 4, 4, 4, 2, 1, 2, 0, 0.75f, 0.55f, 0.0f, 0, 0, 0, 0.89f, 0.0f, 7.5f, 20.0f, 0.96f},
     // few rows (tensor times a matrix with up to 32 rows): half the idle MFMA
     // rows of 64 x 256, four to five workgroups per CU.  C of 24 x 2985984 over
     // 36: 271 -> 188 us, of 24 x 677376 over 96: 99 -> 68 us.
-    {32, 256, 16, 1, 4, 2, 4, 3, 1, 2, 0, 0.66f, 0.60f, 0.0f, 0, 1},
+    {32, 256, 16, 1, 4, 2, 4, 3, 1, 2, 0, 0.66f, 0.60f, 0.0f, 0, 1, 0, 0.0f, 0.0f, 0.55f, 2.7f, 0.96f},
 };
 constexpr TileShape kTilesF64[] = {
     {128, 128, 16, 2, 2, 2, 2, 1, 2, 2, 0, 0.65f, 0.34f, 0.0f},
