@@ -5,6 +5,7 @@ set takes more than one box), and the K block lengths along an index that
 vector gathers run along."""
 import json
 
+import numpy as np
 import pytest
 
 import paper_1607_00145_amd as g
@@ -120,3 +121,16 @@ def test_forced_persistent_kernel_falls_back(monkeypatch):
     assert "scalar" in (d["gather_x"], d["gather_y"]) and d["kernel"] == "macro"
     d = describe(("a,b", "k,a", "k,b"), {"a": 512, "b": 512, "k": 24}, g.GETT_FLOAT64)
     assert d["kernel"] == "direct-stream"
+
+
+@pytest.mark.parametrize("dtype,code", [(np.float32, g.GETT_FLOAT32), (np.float64, g.GETT_FLOAT64)])
+def test_sweeps_over_the_tiles_reach_every_tile(monkeypatch, dtype, code):
+    """The suites that force each tile in turn count them by this table: the
+    index behind its last is no tile any more (the plan's own pick is taken)."""
+    from test_gpu_parity import TILES
+    taken = []
+    for tile in range(TILES[dtype] + 1):
+        monkeypatch.setenv("GETT_FORCE_TILE", str(tile))
+        d = describe(("a,b", "a,k", "k,b"), {"a": 64, "b": 64, "k": 64}, code)
+        taken.append(d["tile"]["id"] == tile)
+    assert taken == [True] * TILES[dtype] + [False]

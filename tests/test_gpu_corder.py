@@ -95,6 +95,29 @@ def test_c_order_every_tile(gpu, monkeypatch, dtype, tile):
     check_case(gpu, rng, modes, shapes(modes, ext), dtype, 1.0, 0.0)
 
 
+@pytest.mark.parametrize("a,c,d", [(4, 17, 19), (16, 5, 9), (24, 3, 9), (28, 3, 11)])
+@pytest.mark.parametrize("name", list(PATTERNS))
+def test_c_order_on_few_rows(gpu, monkeypatch, name, a, c, d):
+    """The 32-row tile: several passes of whole runs per tile, columns left idle
+    behind the last run (runs of 24 and 28), a last tile that is ragged in both
+    directions; bit for bit the per-lane stores."""
+    monkeypatch.setenv("GETT_FORCE_TILE", "9")
+    monkeypatch.setenv("GETT_FORCE_KIND", "0")
+    modes, ext = PATTERNS[name], dict(EXT[np.float32], a=a, c=c, d=d, f=5)
+    plan = describe(modes, ext, np.float32)
+    cols = plan["tile"]["nt"] // a * a
+    assert plan["kernel"] == "macro" and plan["c_order_run"] == a and plan["grid"]["tiles_y"] > 1
+    assert plan["size_x"] % plan["tile"]["mt"] and plan["size_y"] % cols
+    for alpha, beta in [(1.0, 0.0), (1.25, -0.75)]:
+        outs = []
+        for co in ("1", "0"):
+            monkeypatch.setenv("GETT_C_ORDER", co)
+            rng = np.random.default_rng(a)
+            got, _ = check_case(gpu, rng, modes, shapes(modes, ext), np.float32, alpha, beta)
+            outs.append(got.copy())
+        np.testing.assert_array_equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("name", list(PATTERNS))
 def test_lane_order_same_bits(gpu, monkeypatch, name, dtype):

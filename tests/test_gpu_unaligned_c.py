@@ -16,7 +16,7 @@ def shapes(modes, ext):
 
 
 @pytest.mark.parametrize("dtype,tile", [(dt, t) for dt in (np.float32, np.float64)
-                                        for t in range(TILES[dt] + (dt == np.float32))])
+                                        for t in range(TILES[dt])])
 def test_unaligned_c(gpu, monkeypatch, dtype, tile):
     monkeypatch.setenv("GETT_FORCE_TILE", str(tile))
     monkeypatch.setenv("GETT_FORCE_KIND", "0")
