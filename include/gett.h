@@ -178,19 +178,21 @@ gett_status_t gett_plan(gett_plan_t *plan, gett_dtype_t dtype,
  *
  * Workspace.  A plan with K slices or a stream-K tail (gett_plan_describe:
  * "partials": "workspace") saves the partial tiles of a tile's pieces in
- * device memory; the last piece of each tile to finish sums them in piece
- * order and stores the tile (Listing 4 sums the contracted loop in order;
- * this keeps the result independent of timing).  The library owns that
- * memory: one set of buffers per device and stream, allocated (hipMalloc)
+ * device memory.  They are summed in piece order, which keeps the result
+ * independent of timing (Listing 4 sums the contracted loop in order): by the
+ * last piece of each tile to finish, which then stores the tile, or, where the
+ * slices run on the direct-load kernel ("kernel": "direct" with "kslices"
+ * above 1), by a second launch on `stream`, eight slots at a time.  The
+ * library owns that memory: one set of buffers per device and stream, allocated (hipMalloc)
  * by the first call that needs it or more of it, kept until the process
  * ends.  Such a call synchronises `stream` (when buffers grow), and inside a
  * HIP graph capture it is refused: capture a plan's calls after an eager
  * call on the same stream, or use gett_contract_noalloc.  Calls on one stream
  * share its buffers: they run in order, and the launches of one call are
  * enqueued together also when several host threads call on that stream; calls
- * on different streams use different ones.  Errors: GETT_ERROR_HIP also when that allocation fails;
- * GETT_ERROR_NOT_SUPPORTED, with nothing enqueued, when it would have to
- * happen while `stream` is capturing a graph.
+ * on different streams use different ones.  Errors: GETT_ERROR_HIP also when
+ * that allocation fails; GETT_ERROR_NOT_SUPPORTED, with nothing enqueued, when
+ * it would have to happen while `stream` is capturing a graph.
  */
 gett_status_t gett_contract(const gett_plan_t plan, double alpha, const void *A, const void *B,
                             double beta, void *C, void *stream);
@@ -263,15 +265,18 @@ const char *gett_status_string(gett_status_t status);
  * variants), kernel kind ("macro", "stream", "tail", "direct": operands
  * copied from device memory straight into LDS, or "direct-stream": the same,
  * by persistent workgroups that copy the next tile's operands while storing
- * the current tile, or "direct-element": copied element by element), K slices, the
- * stream-K tail's whole tiles, workgroups and boxes per workgroup, how C is
+ * the current tile, or "direct-element": copied element by element; with
+ * "kslices" above 1 "macro" and "direct" name the kernel the slices run on), K
+ * slices, the stream-K tail's whole tiles, workgroups and boxes per workgroup,
+ * how C is
  * accessed ("c_access": "vector", 16-byte vectors on the 16-byte grid; "run",
  * vectors at any element address where columns follow one another in C;
- * "element"), the additions in a row behind an element of C ("chain":
- * one per contracted position, one per partial tile) and those of the model's
- * reference, which the plan does not exceed, whether gett_contract_noalloc takes
- * that reference ("reference_fits"; it then takes the plan too), the partial-tile workspace, grid, the ranked candidates and the flop / byte
- * counts of Eq. 12-14.
+ * "element"), the additions in a row behind an element of C ("chain": one per
+ * contracted position, one per partial tile), the plan of the model without the
+ * price of gathers ("reference", "reference_chain"), whose chain the plan does
+ * not exceed, whether gett_contract_noalloc takes that one ("reference_fits"; it
+ * then takes the plan too), the partial-tile workspace, grid, the ranked
+ * candidates and the flop / byte counts of Eq. 12-14.
  * Returns "" for NULL.
  */
 const char *gett_plan_describe(const gett_plan_t plan);

@@ -1018,8 +1018,9 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         }
         // K slices: when a contracted set of many boxes meets too few tiles to
         // give every SIMD two wavefronts, P workgroups share each tile's
-        // boxes.  Their partial tiles go to the workspace and the last of a
-        // tile's slices to finish sums the P of them in slice order.  Priced
+        // boxes.  Their partial tiles go to the workspace and are summed in
+        // slice order by the last of a tile's slices to finish (on the
+        // direct-load kernel: by a second launch).  Priced
         // like the macro-kernel on tiles * P workgroups with ceil(boxes / P)
         // boxes each plus two boxes' worth of set-up and epilogue per
         // workgroup, plus the partial tiles' traffic, which adds to the time:

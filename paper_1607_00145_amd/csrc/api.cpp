@@ -285,8 +285,8 @@ gett_status_t contract_with(const gett_plan_s &P, double alpha, const void *A, c
     // (streaming walk, beta != 0) runs faster in hardware order (measured).
     if (d.xcdremap < 0) d.xcdremap = (d.order == 1 && beta != 0.0) ? 0 : 1;
     // launch variant: 0 whole tiles, 1 streaming, 2 K slices, 3 stream-K tail,
-    // 4 direct-load, 5 persistent direct-load (one K box)
-    // 6 element-wise direct-load
+    // 4 direct-load, 5 persistent direct-load (one K box), 6 element-wise
+    // direct-load
     int kind = P.kind == 1 || P.kind >= 3 ? P.kind : d.kslices > 1 ? 2 : 0;
     if (!readAB) {   // alpha == 0 or empty sum: C <- beta * C, A and B untouched
         d.nsteps = 0;

@@ -426,10 +426,11 @@ gett_direct_kernel(const KDesc d, const T *__restrict__ X, const T *__restrict__
 // K slices on the direct-load kernel: workgroup b computes slice b / tiles of
 // tile b % tiles into slot b of the workspace (the slots of the macro-kernel's
 // K slices), and gett_sum_slices_kernel adds a tile's slots in slice order.
-// Bound by the MFMAs: a C of 384 x 376 over 144384 is 9 tiles of 128 x 128,
-// 56 slices of which fill the CUs twice, against 72 tiles of 32 x 64 (64
-// slices), the largest for which the last workgroup of a tile can sum its
-// slots in turn without dominating.  432 us on those, 351 us here.
+// Bound by the MFMAs: a C of 384 x 376 over 144384 is 9 tiles of 128 x 128
+// against 72 tiles of 32 x 64 (64 slices), the largest for which the last
+// workgroup of a tile can sum its slots in turn without dominating: 431 us on
+// those, 336 here in 56 slices, which fill the CUs twice, 342 in 113, whose
+// sums are as short as those of the small tiles.
 // Consecutive workgroups of one XCD share a slice's panels in its L2.
 template <typename T, int MT, int NT, int KT, int WM, int WN, int RX, int RY, int XMODE,
           int YMODE, bool WHOLE>

@@ -37,7 +37,8 @@ constexpr uint64_t kFixedCounters = 1u << 16;
 // A kernel candidate: tile shape and kind, with the model's estimate.
 struct Candidate {
     int tile = 0, kind = 0;                 // kind 0: macro-kernel, 1: streaming kernel,
-                                            // 2: macro-kernel over K slices,
+                                            // 2: K slices, on the direct-load kernel
+                                            // where direct_slices() says, else macro,
                                             // 3: stream-K tail kernel,
                                             // 4: direct-load kernel,
                                             // 5: persistent direct-load kernel,
@@ -107,7 +108,7 @@ struct gett_plan_s {
     int tile;                // index into the tile table of the dtype
     int xmode, ymode;        // gather modes of the preferred kernel
     int kind;                // 0: macro-kernel, 1: persistent streaming kernel,
-                             // 2: macro-kernel over K slices (desc.kslices > 1),
+                             // 2: K slices (desc.kslices > 1), see Candidate,
                              // 3: stream-K tail kernel (desc.tailFull ...),
                              // 4: direct-load kernel, 5: persistent, 6: element-wise
     std::vector<gett::Candidate> ranked;   // every candidate, best model estimate first
@@ -157,10 +158,11 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
 gett_status_t contract_with(const gett_plan_s &P, double alpha, const void *A, const void *B,
                             double beta, void *C, hipStream_t stream, WorkspaceFn ws);
 
-// "macro", "stream", "kslices", "tail" or "direct" (Candidate::kind).
+// "macro", "stream", "kslices", "tail", "direct", "direct-stream" or
+// "direct-element" (Candidate::kind).
 const char *kind_name(int kind);
-// Launch table lookup (defined with the kernel instantiations).  kind 0: the
-// macro-kernel, 1: the persistent streaming kernel.
+// Launch table lookup (defined with the kernel instantiations); kind as in
+// Candidate.
 LaunchFn launch_fn(gett_dtype_t dtype, int tile, int xmode, int ymode, int kind);
 
 }  // namespace gett

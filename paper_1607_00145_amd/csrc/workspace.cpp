@@ -1,12 +1,12 @@
 // workspace.cpp -- device workspace for the partial tiles of K slices and of
 // the stream-K tail (kernel.hpp: a tile's pieces are saved and summed in
-// piece order by the last to finish).
+// piece order by the last to finish; direct.hpp: summed by a second launch).
 //
 // One pair of buffers per (device, stream): per-tile counters, zeroed when
 // allocated and left at zero by every launch that uses them, and the
 // partial-tile slots, which need no initial value.  Launches on one stream
-// run in order, so they can share the pair; launches on different streams get
-// different pairs.  A buffer grows when a plan needs more: the stream is
+// run in order and a call holds the pair until its launches are enqueued, so
+// they can share it; launches on different streams get different pairs.  A buffer grows when a plan needs more: the stream is
 // synchronised first (queued work may still use the old one).  Growth is
 // refused (GETT_ERROR_NOT_SUPPORTED, nothing enqueued) while the stream is
 // capturing a graph -- an eager call of the plan on that stream beforehand
