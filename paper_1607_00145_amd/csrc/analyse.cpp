@@ -869,15 +869,20 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         // second on every tile and kernel that fills the CUs (each row of tiles
         // reads all of Y again; 136 x 197 x 56 fp32 over 176: 54 us on tiles of 32
         // rows, 32 on 64).  Where the lane order groups the columns by a first
-        // index shorter than the tile, up to twice as many.
+        // index shorter than the tile, up to twice as many.  In fp64 only where whole
+        // tiles leave CUs idle, the one place where it was measured to decide
+        // (120 x 109 x 7 over 128: 22.9 us on 109 tiles of 32 x 64, 13.3 on 218 of
+        // 64 x 32).
         const double group = (double)c.nt / (double)std::max<int64_t>(Iy[0].extent, 1);
         const bool grouped = group >= 1.0 && (4.0 * bytesY >= bytesC || yUnit == 1);
         const double apartRate = 1.0e12 * (0.17 + (grouped ? 0.024 * group : 0.0)) *
                                  (c.nt >= 256 ? 0.8 : 1.0);
         auto apart = [&](double wgs) {
-            if (!gathers || dtype != GETT_FLOAT32 || vecY || vecYSplit || yUnit < 1) return 0.0;
-            return (double)sizeY * (double)an.sizeK * tx /
-                   (apartRate * std::min(1.0, std::max(wgs, 1.0) * wpt / 1024.0));
+            const double share = std::min(1.0, std::max(wgs, 1.0) * wpt / 1024.0);
+            if (!gathers || (dtype != GETT_FLOAT32 && share == 1.0) || vecY || vecYSplit ||
+                yUnit < 1)
+                return 0.0;
+            return (double)sizeY * (double)an.sizeK * tx / (apartRate * share);
         };
         const double tApart = apart(tx * ty);
         // The persistent streaming kernel needs the contracted set in one box.
@@ -1080,7 +1085,8 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
                 // (3, 6, .. 192 slices keep a chain or the workspace's limit that
                 // powers of two may not; they take longer than priced: 66 x 72 over
                 // 5184 fp64 26.9 us in 48, 22.4 in 32)
-                cd.cost = (bound(std::max({tM, tMemP, apart(wgs)}), tChainP) + tPart) *
+                cd.cost = (bound(std::max({tM, tMemP, dtype == GETT_FLOAT32 ? apart(wgs) : 0.0}),
+                                 tChainP) + tPart) *
                           (!directSlices && (P & (P - 1)) ? 1.25 : 1.0);
                 if (better(cd, best)) best = cd;
             }

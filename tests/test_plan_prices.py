@@ -98,8 +98,20 @@ MEASURED = [
       ("macro", 9, 1): 315.6}),
 ]
 
+# fp64, beta = 0.5: tiles that leave CUs idle, Y gathered in single elements
+MEASURED_F64 = [
+    ("abc-bda-dc", {"a": 120, "b": 109, "c": 7, "d": 128}, 0,
+     {("macro", 12, 1): 13.3, ("macro", 13, 1): 22.9}),
+    ("abc-bda-dc", {"a": 121, "b": 112, "c": 8, "d": 128}, 3,
+     {("macro", 12, 1): 14.4, ("macro", 13, 1): 24.3}),
+    ("abc-bda-dc", {"a": 90, "b": 99, "c": 6, "d": 88}, 0,
+     {("macro", 12, 1): 10.3, ("macro", 13, 1): 15.5}),
+    ("abc-bda-dc", {"a": 77, "b": 92, "c": 5, "d": 74}, 8,
+     {("macro", 12, 1): 8.3, ("macro", 13, 1): 12.2}),
+]
 
-def describe(pattern, ext, pad):
+
+def describe(pattern, ext, pad, dtype=g.GETT_FLOAT32):
     C, A, B = pattern.split("-")
     args = []
     for m in (C, A, B):
@@ -109,7 +121,7 @@ def describe(pattern, ext, pad):
             stride.append(acc)
             acc *= e + (pad if i == 0 else 0)
         args += [",".join(m), shape, stride]
-    st, h = g.gett_plan(g.GETT_FLOAT32, *args, 0)
+    st, h = g.gett_plan(dtype, *args, 0)
     assert st == 0
     try:
         return json.loads(g.gett_plan_describe(h))
@@ -117,11 +129,21 @@ def describe(pattern, ext, pad):
         g.gett_destroy(h)
 
 
-@pytest.mark.parametrize("pattern,ext,pad,times", MEASURED,
-                         ids=[p + "-" + "x".join(str(e) for e in x.values())
-                              for p, x, _, _ in MEASURED])
-def test_pick_is_near_the_best(pattern, ext, pad, times):
-    d = describe(pattern, ext, pad)
+def check(d, times):
     pick = (d["kernel"], d["tile"]["id"], d["kslices"])
     assert pick in times, (pick, sorted(times.items(), key=lambda t: t[1])[:3])
     assert times[pick] <= 1.10 * min(times.values()), (pick, times[pick], min(times.values()))
+
+
+def names(table):
+    return [p + "-" + "x".join(str(e) for e in x.values()) for p, x, _, _ in table]
+
+
+@pytest.mark.parametrize("pattern,ext,pad,times", MEASURED, ids=names(MEASURED))
+def test_pick_is_near_the_best(pattern, ext, pad, times):
+    check(describe(pattern, ext, pad), times)
+
+
+@pytest.mark.parametrize("pattern,ext,pad,times", MEASURED_F64, ids=names(MEASURED_F64))
+def test_pick_is_near_the_best_f64(pattern, ext, pad, times):
+    check(describe(pattern, ext, pad, g.GETT_FLOAT64), times)
