@@ -907,15 +907,20 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const double a = tput * tput, b = lat * lat;
             return std::sqrt(std::sqrt(a * a + b * b));
         };
+        // Bytes of the stream, C's counted `cut` times.  (A candidate's tMem counts
+        // them once: whether C's stream bounds it decides the walk below.)
+        auto bytes = [&](double cut) {
+            return bytesC * cut + bytesX + bytesY +
+                   0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1));
+        };
         for (int k = 0; k < (canStream ? 2 : 1); ++k) {
             const double bwFrac = (k ? c.sbw : c.bw) * cuShare;
             // compulsory bytes (each operand read once, C written once) plus
             // the operand panels re-read by other tiles, mostly from L2
             // A single LDS buffer does not overlap the boxes of an fp64 stream
             // (C of 24 x 373248 over 72: 82 us on 64 x 128, 60 on 32 x 64).
-            const double tMem = (bytesC * (k == 0 && run > 0 ? 1.0 : cutC) + bytesX + bytesY +
-                                 0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
-                                (8.0e12 * bwFrac) *
+            const double cut = k == 0 && run > 0 ? 1.0 : cutC;
+            const double tMem = bytes(cut) / (8.0e12 * bwFrac) *
                                 (!gathers || dtype != GETT_FLOAT64      ? 1.0
                                  : c.nbuf == 1 && b.nsteps > 1          ? 1.4
                                  : elements && c.mt * c.nt <= 32 * 64 ? 1.25
@@ -925,7 +930,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             cd.kind = k;
             const double idle = run > 0 && k == 0 ? (double)c.nt / (double)(c.nt / run * run) : 1.0;
             cd.tMfma = idle > 1.0 ? tMfma * per_simd(tx * tyRun) / perSimdRun : tMfma;
-            cd.tMem = tMem * idle;
+            cd.tMem = tMem * idle / bytes(cut) * bytes(1.0);
             // element-wise gathers into a single LDS buffer (the streaming
             // kernel too) wait with nothing to overlap them, as in the K split
             // (the fp32 tiles 256 wide carry sixteen such loads per thread and
@@ -948,7 +953,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             const double setup = set_up(false);
             const double restHere = run > 0 && k == 0 ? std::max(rest, 0.95) : rest;
             cd.cost = bound(std::max({cd.tMfma * single * restHere + setup,
-                                      cd.tMem * single + 0.25 * setup, tApart}),
+                                      tMem * idle * single + 0.25 * setup, tApart}),
                             tChain);
             ranked.push_back(cd);
         }
@@ -962,16 +967,14 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             (!gathers      ? !slowGather && !kSplitAhead
              : kSplitAhead ? aligned(Ix, sX, -1)
                            : vecXHere && vecY)) {
-            const double tMem = (bytesC * cutC + bytesX + bytesY +
-                                 0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
-                                (8.0e12 * c.bw * cuShare);
+            const double tMem = bytes(cutC) / (8.0e12 * c.bw * cuShare);
             Candidate cd;
             cd.tile = t;
             cd.kind = 4;
             cd.chain = oneChain;
             cd.tMfma = tMfma / kSplitWait * c.eff / c.deff *
                        (gathers ? (kSplitAhead ? 1.12 : 1.11) : 1.0);
-            cd.tMem = tMem;
+            cd.tMem = tMem / bytes(cutC) * bytes(1.0);
             cd.cost = bound(std::max(cd.tMfma + set_up(wpt < 8), tMem + 0.25 * set_up(wpt < 8)),
                             tChain);
             ranked.push_back(cd);
@@ -983,9 +986,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
         if (gathers && c.deff > 0.0f && dtype == GETT_FLOAT32 && !(vecX && vecY) &&
             !kSplitAhead && !an.emptySum && an.sizeK < INT32_MAX / 2 && an.maxOffA < INT32_MAX &&
             an.maxOffB < INT32_MAX) {
-            const double tMem = (bytesC * cutC + bytesX + bytesY +
-                                 0.05 * (bytesX * (ty - 1) + bytesY * (tx - 1))) /
-                                (8.0e12 * c.bw * cuShare);
+            const double tMem = bytes(cutC) / (8.0e12 * c.bw * cuShare);
             const double boxes = std::ceil((double)an.sizeK / c.kt);
             Candidate cd;
             cd.tile = t;
@@ -993,7 +994,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             cd.chain = oneChain;
             cd.tMfma = tMfma * boxes * c.kt / kpad / kElementWise * c.eff /
                        (wpt >= 8 ? 0.80 : 0.75) * (crossed && c.mt < 256 ? 1.4 : 1.0);
-            cd.tMem = tMem;
+            cd.tMem = tMem / bytes(cutC) * bytes(1.0);
             cd.cost = bound(std::max({cd.tMfma + set_up(wpt < 8), tMem + 0.25 * set_up(wpt < 8),
                                       tApart}),
                             chain(tx * ty, boxes));
