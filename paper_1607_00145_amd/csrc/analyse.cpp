@@ -244,6 +244,12 @@ static double tail_occupancy(const TileShape &c, double itemB)
 // gathers and LDS reads).
 static double cu_time(int occ, int full, double nb, int tail, double len)
 {
+    // equal runs finish together: whole rounds, and a last one at the rate of
+    // what is left of it
+    if (tail == 0) {
+        const bool lone = occ >= 2 && full % std::min(occ, 8) == 1;
+        return nb * (lone ? full - 1 + 1.0 / 0.64 : full);
+    }
     // (at most eight wavefronts per SIMD, so at most eight workgroups here)
     double left[8];
     int held = 0, next = 0;
@@ -766,6 +772,7 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
     // or, for the reference below, as if every tile gathered alike.
     auto candidates = [&](bool gathers) {
     std::vector<Candidate> ranked;
+    ranked.reserve(64);
     for (int t = 0; t < num_tiles(dtype); ++t) {
         const TileShape &c = tile_shape(dtype, t);
         if (!gathers && c.nt >= 8 * c.mt) continue;   // the tile for few rows: by its gathers only
@@ -1047,18 +1054,19 @@ gett_status_t analyse(gett_plan_s &plan, gett_dtype_t dtype, const char *mC, con
             // in 64: 431 us, 8.6e-7).
             const bool directSlices =
                 gathers && c.deff > 0.0f && vecXHere && vecY && !kSplitAhead;
-            std::vector<int> counts;
+            int counts[24], ncounts = 0;
             for (int P = 2; P <= 256; P *= 2) {
-                counts.push_back(P);
-                if (gathers && inPieces && P < 256) counts.push_back(P + P / 2);
+                counts[ncounts++] = P;
+                if (gathers && inPieces && P < 256) counts[ncounts++] = P + P / 2;
             }
             if (directSlices) {
                 const double resident = wpt >= 8 ? 256.0 : 512.0;
                 if (resident / (tx * ty) >= 2.0)
                     for (int fill = 1; fill <= 3; ++fill)
-                        counts.push_back((int)(fill * resident / (tx * ty)));
+                        counts[ncounts++] = (int)(fill * resident / (tx * ty));
             }
-            for (int P : counts) {
+            for (int i = 0; i < ncounts; ++i) {
+                const int P = counts[i];
                 if (b.nsteps / P < 8) continue;
                 const double wgs = tx * ty * P;
                 const double perSimdP = per_simd(wgs);
